@@ -314,7 +314,8 @@ pg_status pg_uv_prune(const float* params, const int64_t* n_gauss_dev, int64_t n
  *   flow_masks   device uint8 [n_pixels]: view v's [H_v][W_v] mask at its
  *                pixel base; non-zero = motion
  *   tile_motion  device uint8 [n_tiles] workspace: which screen tiles of the
- *                view table hold motion (filled by the call)
+ *                view table hold motion (filled by the call; non-zero: some
+ *                pixel of the tile is set)
  *   dyn_gauss    device uint8 [F][n_gauss] out: D per frame and Gaussian
  *   texel_gauss  device int32 [H W] (from pg_atlas_fetch); read only with
  *   dyn_texel    device uint8 [H W] out or NULL: 1 where the texel's Gaussian

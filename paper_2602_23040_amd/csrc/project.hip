@@ -428,33 +428,89 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
 // is within r = ceil(3 sqrt(lambda_max)) of the mean on both axes and inside
 // the image has q <= 9 and a non-zero flow mask (the OR across cameras).
 //
-// k_tile_motion marks the screen tiles holding any motion (one wave per
-// tile).  k_flow_mask then runs one thread per (view, Gaussian) record: the
-// projection chain, culls and radius of k_project; the record stops there
-// unless a tile under its square has motion.  The square is then scanned by
-// the whole wave: the wave takes its flagged records one by one and tests 64
-// pixels per round, only in tiles that hold motion (elsewhere the mask is
-// zero), the mask byte first and q <= 9 in FP64 at the pixel centre, so the
-// label is exactly that of a scan of every pixel of the square.  (One thread
-// walking its own rows left the other lanes of its wave idle and issued one
-// dependent mask load per pixel: 2.6 ms against 1.2 ms on 50 views.)  A hit
-// writes 1 to the Gaussian's zeroed label: every writer stores the same
-// value, so the OR over views needs no atomics.
-__global__ __launch_bounds__(64) void k_tile_motion(const ViewDev* __restrict__ views, int nv, int64_t n_tiles,
-                                                    int32_t tw, int32_t th, const uint8_t* __restrict__ masks,
-                                                    uint8_t* __restrict__ tmot) {
-    const int64_t tile = blockIdx.x;
-    if (tile >= n_tiles) return;
-    const ViewDev& V = views[find_view_by_tile(views, nv, tile)];
-    const int64_t local = tile - V.tile_base;
-    const int32_t ty = (int32_t)(local / V.TX), tx = (int32_t)(local - (int64_t)ty * V.TX);
+// k_tile_motion marks the cells of 8 x 4 pixels holding any motion, a byte per
+// screen tile.  k_flow_mask then works in two phases per work-group (one view, kFlowRecs Gaussians):
+//  1. An FP32 bound per record: a disc around the mean that contains the exact
+//     square (the largest scale through the Jacobian's norm, every rounding
+//     covered), and whether a motion cell lies under it.  Most records end
+//     here after ~80 instructions instead of the FP64 projection's ~450, and a
+//     Gaussian that an earlier view has already labelled ends at once.
+//  2. The records left are collected in LDS, so that every lane has one: the
+//     FP64 projection, culls and radius of k_project, and the cells under the
+//     ellipse's box.  Then eight lanes take a record and scan the box's rows
+//     from the middle out, eight mask bytes per load, with q <= 9 in FP64 at
+//     the centres whose mask is set.  The label is exactly that of a scan of
+//     every pixel of the square.  (One lane per record waits for the largest
+//     box among 64: 730 us against 482.)  Squares past kFlowSide are scanned by
+//     the whole wave, 64 pixels per round, only in tiles that hold motion.
+// A hit writes 1 to the Gaussian's zeroed label: every writer stores the same
+// value, so the OR over views needs no atomics.  A Gaussian's chunk runs on one
+// XCD for every view, so its parameters and labels stay in that L2.
+// 14.0 M records of 50 views of 1024x768, 3 % of motion: the whole call 1,720 us
+// with the FP64 projection of every record and a wave per flagged record; 575
+// with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles
+// (of which the fetch, the cells and the first phase are 260).
+constexpr int kFlowThreads = 256;
+constexpr int kFlowRecs = 2048;        // Gaussians per work-group
+constexpr int kFlowSide = 64;          // largest side of a square that eight lanes scan
+
+// Eight mask bytes from p on (zero past the end of the masks).
+__device__ __forceinline__ uint64_t mask8(const uint8_t* __restrict__ masks, int64_t p, int64_t n) {
+    uint64_t w = 0;
+    if (p + 8 <= n) {
+        __builtin_memcpy(&w, masks + p, 8);
+    } else {
+        for (int k = 0; p + k < n; k++) w |= (uint64_t)masks[p + k] << (8 * k);
+    }
+    return w;
+}
+__device__ __forceinline__ uint64_t first_bytes(uint64_t w, int32_t n) {
+    return n >= 8 ? w : (n > 0 ? w & ((1ull << (8 * n)) - 1) : 0ull);
+}
+
+// A tile is 256 pixels, 32 runs of eight: half a wave per tile, one run per lane.
+// The tile's byte has a bit per cell of 8 x 4 pixels (row-major) that holds motion.
+__global__ __launch_bounds__(256) void k_tile_motion(const ViewDev* __restrict__ views, int nv, int64_t n_tiles,
+                                                     int64_t n_pixels, int32_t tw,
+                                                     const uint8_t* __restrict__ masks, uint8_t* __restrict__ tmot) {
+    const int64_t tile = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
+    const int32_t runs = tw / 8, th = 256 / tw;
     bool any = false;
-    for (int32_t k = threadIdx.x; k < tw * th; k += 64) {
-        const int32_t x = tx * tw + k % tw, y = ty * th + k / tw;
-        if (x < V.W && y < V.H) any |= masks[V.pix_base + (int64_t)y * V.W + x] != 0;
+    if (tile < n_tiles) {
+        const ViewDev& V = views[find_view_by_tile(views, nv, tile)];
+        const int64_t local = tile - V.tile_base;
+        const int32_t ty = (int32_t)(local / V.TX), tx = (int32_t)(local - (int64_t)ty * V.TX);
+        const int32_t k = (int32_t)(threadIdx.x % 32);
+        const int32_t x = tx * tw + (k % runs) * 8, y = ty * th + k / runs;
+        if (x < V.W && y < V.H)
+            any = first_bytes(mask8(masks, V.pix_base + (int64_t)y * V.W + x, n_pixels), V.W - x) != 0;
     }
     const uint64_t b = __ballot(any);
-    if (threadIdx.x == 0) tmot[tile] = b ? 1 : 0;
+    uint32_t h = (uint32_t)(threadIdx.x & 32 ? b >> 32 : b);
+    h |= h >> runs;             // four rows of runs into one
+    h |= h >> (2 * runs);
+    uint32_t cells = 0;
+    for (int32_t r = 0; r < th / 4; r++) cells |= ((h >> (4 * r * runs)) & ((1u << runs) - 1u)) << (r * runs);
+    if (tile < n_tiles && threadIdx.x % 32 == 0) tmot[tile] = (uint8_t)cells;
+}
+
+// Whether a cell under the pixels [x0, x1] x [y0, y1] (inside the view) holds motion.
+__device__ __forceinline__ bool motion_under(const ViewDev& V, const uint8_t* __restrict__ tmot, int32_t x0, int32_t x1,
+                                             int32_t y0, int32_t y1, int32_t tw, int32_t th) {
+    const int32_t runs = tw / 8, sx = __builtin_ctz(tw), sy = __builtin_ctz(th);
+    const uint32_t rep = runs == 1 ? 0xffu : (runs == 2 ? 0x55u : 0x11u);       // a row's columns in every row
+    uint32_t any = 0;
+    for (int32_t ty = y0 >> sy; ty <= y1 >> sy; ty++) {
+        const int32_t r0 = max(y0 - (ty << sy), 0) >> 2, r1 = min(y1 - (ty << sy), th - 1) >> 2;
+        const uint32_t rows = (1u << ((r1 + 1) * runs)) - (1u << (r0 * runs));
+        const uint8_t* row = tmot + V.tile_base + (int64_t)ty * V.TX;
+#pragma unroll 2
+        for (int32_t tx = x0 >> sx; tx <= x1 >> sx; tx++) {
+            const int32_t c0 = max(x0 - (tx << sx), 0) >> 3, c1 = min(x1 - (tx << sx), tw - 1) >> 3;
+            any |= row[tx] & rows & (((2u << c1) - (1u << c0)) * rep);
+        }
+    }
+    return any != 0;
 }
 
 __global__ void k_fill_u8(uint8_t* __restrict__ p, int64_t n) {
@@ -462,96 +518,211 @@ __global__ void k_fill_u8(uint8_t* __restrict__ p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-__global__ __launch_bounds__(128) void k_flow_mask(const ViewDev* __restrict__ views, int32_t C, int64_t N,
-                                                   int64_t n_gv, int32_t tw, int32_t th,
-                                                   const float* __restrict__ params,
-                                                   const uint8_t* __restrict__ masks,
-                                                   const uint8_t* __restrict__ tmot, uint8_t* __restrict__ dyn_gauss,
-                                                   unsigned long long* __restrict__ counters) {
-    // work-group b takes records [c * 128, c * 128 + 128) of view b / chunks (c = b mod
-    // chunks): the view, so its camera, is uniform over the work-group (scalar loads)
-    const int64_t chunks = (N + 127) / 128;
-    const int32_t v = (int32_t)((int64_t)blockIdx.x / chunks);
-    const int64_t i = ((int64_t)blockIdx.x - (int64_t)v * chunks) * 128 + threadIdx.x;
+// False when the record is certainly static in this view: culled by depth, or
+// no motion cell under a square that contains the exact one.
+// e = 2^-21 bounds eight FP32 roundings; each quantity carries its own bound.
+__device__ __forceinline__ bool flow_may_hit(const ViewDev& V, float rn2, const float* __restrict__ P, int64_t N,
+                                             int32_t tw, int32_t th, const uint8_t* __restrict__ tmot) {
+    constexpr float e = 4.76837158e-7f;
+    const float x = P[0], y = P[N], z = P[2 * N];
+    const float ls = fmaxf(fmaxf(P[3 * N], P[4 * N]), P[5 * N]);
+    const float* R = V.Rf;
+    const float xc = fmaf(R[0], x, fmaf(R[1], y, fmaf(R[2], z, V.tf[0])));
+    const float yc = fmaf(R[3], x, fmaf(R[4], y, fmaf(R[5], z, V.tf[1])));
+    const float zc = fmaf(R[6], x, fmaf(R[7], y, fmaf(R[8], z, V.tf[2])));
+    const float ax = fabsf(x), ay = fabsf(y), az = fabsf(z);
+    auto mag = [&](int r) {
+        return fmaf(fabsf(R[3 * r]), ax, fmaf(fabsf(R[3 * r + 1]), ay, fmaf(fabsf(R[3 * r + 2]), az, fabsf(V.tf[r]))));
+    };
+    const float ex = e * mag(0), ey = e * mag(1), ez = e * mag(2);
+    if (zc + ez < 0.19999f) return false;           // z_c <= 0.2: culled
+    const float zl = fmaxf(zc - ez, 0.19f);         // every z_c that is kept is at least this
+    const float iz = 1.0f / zl;
+    const float u = (fabsf(xc) + ex) * iz, v = (fabsf(yc) + ey) * iz;       // |x_c / z_c| at most
+    const float fu = V.fxf * iz, fv = V.fyf * iz;
+    // largest eigenvalue of J J^T, times the largest eigenvalue of the camera-space covariance
+    const float a = fu * fu * (1.0f + u * u), d = fv * fv * (1.0f + v * v), b = fu * fv * u * v;
+    const float jj = 0.5f * (a + d + sqrtf((a - d) * (a - d) + 4.0f * b * b));
+    const float lam = jj * rn2 * __expf(2.0f * ls) * 1.001f + 0.3001f;
+    // the mean's bound: both ends of z_c's interval, and the roundings of f x / z + c
+    const float izc = 1.0f / fmaxf(zc, 0.19f);
+    const float px = V.fxf * xc * izc + (float)V.cx, py = V.fyf * yc * izc + (float)V.cy;
+    const float r = 3.0015f * sqrtf(lam) + 1.01f;
+    const float rx = r + 2.0f * (fu * (ex + u * ez) + e * (V.fxf * u + fabsf((float)V.cx)));
+    const float ry = r + 2.0f * (fv * (ey + v * ez) + e * (V.fyf * v + fabsf((float)V.cy)));
+    const float fx0 = px - rx, fx1 = px + rx, fy0 = py - ry, fy1 = py + ry;
+    if (fx1 < 0.0f || fx0 > (float)V.W || fy1 < 0.0f || fy0 > (float)V.H) return false;
+    // a square over many tiles, or a bound that is not a number, goes to the exact test
+    if (!(rx < 256.0f && ry < 256.0f && fabsf(px) < 1e8f && fabsf(py) < 1e8f)) return true;
+    const int32_t x0 = (int32_t)fmaxf(fx0, 0.0f), y0 = (int32_t)fmaxf(fy0, 0.0f);
+    return motion_under(V, tmot, min(x0, V.W - 1), min((int32_t)fx1, V.W - 1), min(y0, V.H - 1), min((int32_t)fy1, V.H - 1),
+                        tw, th);
+}
+
+// A record's clipped square and quadratic form (x1 < x0: nothing to scan).
+struct Square {
+    double mx, my, A, B, C;
+    int32_t x0, y0, x1, y1;
+};
+
+__global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __restrict__ views, int32_t nv, int32_t C,
+                                                            int64_t N, int64_t n_pixels, int32_t tw, int32_t th,
+                                                            const float* __restrict__ params,
+                                                            const uint8_t* __restrict__ masks,
+                                                            const uint8_t* __restrict__ tmot, uint8_t* dyn_gauss,
+                                                            unsigned long long* __restrict__ counters) {
+    __shared__ uint16_t s_rec[kFlowRecs];
+    __shared__ Square s_sq[kFlowThreads];
+    __shared__ int32_t s_count;
+    // work-group b runs on XCD b mod 8: chunks of Gaussians are dealt to the XCDs,
+    // and an XCD takes its chunks view by view
+    const int64_t chunks = ceil_div(N, kFlowRecs), per = ceil_div(chunks, 8);
+    const int64_t j = blockIdx.x / 8, c = (int64_t)(blockIdx.x % 8) + 8 * (j % per);
+    const int32_t v = (int32_t)(j / per);
+    if (c >= chunks || v >= nv) return;
+    const ViewDev& V = views[v];
     const int lane = (int)(threadIdx.x & 63);
+    const int64_t i0 = c * kFlowRecs;
+    const float* P0 = params + (int64_t)V.frame * C * N;
+    const int64_t out0 = (int64_t)V.frame * N;
     uint64_t tests = 0;
-    // this thread's record: projection, clipped square and the motion-tile test
-    bool any = false;
-    int32_t ix0 = 0, ix1 = -1, iy0 = 0, iy1 = -1;
-    int64_t out = 0;
-    double mx = 0.0, my = 0.0, A = 1.0, B = 0.0, Cq = 1.0;
-    if (i < N) {
-        const ViewDev& V = views[v];
-        out = (int64_t)V.frame * N + i;
-        const float* P = params + (int64_t)V.frame * C * N + i;
-        float rec[11];
+    if (threadIdx.x == 0) s_count = 0;
+    // |R R^T| bounds the squared norm of the camera matrix (1 for a rotation)
+    float rn2 = 0.0f;
 #pragma unroll
-        for (int k = 0; k < 11; k++) rec[k] = P[(int64_t)k * N];
-        World w;
-        world_chain(rec, w);
-        Cam c;
-        if (camera_chain(V, w, c) && c.det > kDetMin) {
-            const double tr = c.ap + c.cp;
-            const double lam = 0.5 * (tr + sqrt(fmax(0.0, tr * tr - 4.0 * c.det)));
-            const double rr = ceil(3.0 * sqrt(lam));
-            mx = (V.fx * c.xc) / c.zc + V.cx;
-            my = (V.fy * c.yc) / c.zc + V.cy;
-            const double x0 = fmax(0.0, ceil(mx - rr - 0.5)), x1 = fmin((double)(V.W - 1), floor(mx + rr - 0.5));
-            const double y0 = fmax(0.0, ceil(my - rr - 0.5)), y1 = fmin((double)(V.H - 1), floor(my + rr - 0.5));
-            if (x0 <= x1 && y0 <= y1) {
-                ix0 = (int32_t)x0;
-                ix1 = (int32_t)x1;
-                iy0 = (int32_t)y0;
-                iy1 = (int32_t)y1;
-                for (int32_t ty = iy0 / th; ty <= iy1 / th && !any; ty++)
-                    for (int32_t tx = ix0 / tw; tx <= ix1 / tw; tx++)
-                        if (tmot[V.tile_base + (int64_t)ty * V.TX + tx]) {
-                            any = true;
-                            break;
-                        }
-            }
-            if (any) {
-                A = c.cp / c.det;
-                B = -c.bp / c.det;
-                Cq = c.ap / c.det;
-            }
-        }
+    for (int r = 0; r < 3; r++) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+            sum += fabsf(fmaf(V.Rf[3 * r], V.Rf[3 * k], fmaf(V.Rf[3 * r + 1], V.Rf[3 * k + 1], V.Rf[3 * r + 2] * V.Rf[3 * k + 2])));
+        rn2 = fmaxf(rn2, sum);
     }
-    // The wave scans its flagged records one after another, all lanes on one
-    // record: per motion tile under the record's square, 64 pixels per round,
-    // the mask byte first and q <= 9 (FP64, at the pixel centre) only where it
-    // is set; a ballot ends the record at its first hit.  Every pixel centre
-    // of the clipped square lies in one of these tiles or has a zero mask.
-    uint64_t todo = __ballot(any);
-    while (todo) {
-        const int src = __builtin_ctzll(todo);
-        todo &= todo - 1;
-        const int32_t rv = v;
-        const int32_t sx0 = __shfl(ix0, src, 64), sx1 = __shfl(ix1, src, 64);
-        const int32_t sy0 = __shfl(iy0, src, 64), sy1 = __shfl(iy1, src, 64);
-        const double smx = __shfl(mx, src, 64), smy = __shfl(my, src, 64);
-        const double sA = __shfl(A, src, 64), sB = __shfl(B, src, 64), sC = __shfl(Cq, src, 64);
-        const ViewDev& V = views[rv];
-        const uint8_t* M = masks + V.pix_base;
-        const int32_t per_tile = tw * th;
-        bool found = false;
-        for (int32_t ty = sy0 / th; ty <= sy1 / th && !found; ty++) {
-            for (int32_t tx = sx0 / tw; tx <= sx1 / tw && !found; tx++) {
-                if (!tmot[V.tile_base + (int64_t)ty * V.TX + tx]) continue;
-                for (int32_t b = 0; b < per_tile && !found; b += 64) {
-                    const int32_t p = b + lane;
-                    const int32_t x = tx * tw + p % tw, y = ty * th + p / tw;
-                    bool hit = false;
-                    if (p < per_tile && x >= sx0 && x <= sx1 && y >= sy0 && y <= sy1 && M[(int64_t)y * V.W + x]) {
-                        tests++;
-                        hit = q_at(sA, sB, sC, ((double)x + 0.5) - smx, ((double)y + 0.5) - smy) <= 9.0;
+    __syncthreads();
+    // ---- phase 1
+    for (int k = threadIdx.x; k < kFlowRecs; k += kFlowThreads) {
+        const int64_t i = i0 + k;
+        bool keep = i < N;
+        // labelled by an earlier view (a stale 0 only costs the test; with the test
+        // counter the labels are not looked at, so the count is the same every time)
+        const bool labelled = keep && !counters &&
+            __hip_atomic_load(dyn_gauss + out0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
+        if (keep) keep = flow_may_hit(V, rn2, P0 + i, N, tw, th, tmot) && !labelled;
+        const uint64_t m = __ballot(keep);
+        int32_t at = 0;
+        if (lane == 0 && m) at = atomicAdd(&s_count, (int32_t)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (keep) s_rec[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = (uint16_t)k;
+    }
+    __syncthreads();
+    // ---- phase 2
+    const int32_t count = s_count;
+    for (int32_t base = 0; base < count; base += kFlowThreads) {
+        const int32_t at = base + (int32_t)threadIdx.x;
+        bool large = false;
+        int32_t ix0 = 0, ix1 = -1, iy0 = 0, iy1 = -1;
+        int64_t out = 0;
+        double mx = 0.0, my = 0.0, A = 1.0, B = 0.0, Cq = 1.0;
+        if (at < count) {
+            const int64_t i = i0 + s_rec[at];
+            out = out0 + i;
+            float rec[11];
+#pragma unroll
+            for (int k = 0; k < 11; k++) rec[k] = P0[(int64_t)k * N + i];
+            World w;
+            world_chain(rec, w);
+            Cam cam;
+            if (camera_chain(V, w, cam) && cam.det > kDetMin) {
+                const double tr = cam.ap + cam.cp;
+                const double lam = 0.5 * (tr + sqrt(fmax(0.0, tr * tr - 4.0 * cam.det)));
+                const double rr = ceil(3.0 * sqrt(lam));
+                mx = (V.fx * cam.xc) / cam.zc + V.cx;
+                my = (V.fy * cam.yc) / cam.zc + V.cy;
+                const double x0 = fmax(0.0, ceil(mx - rr - 0.5)), x1 = fmin((double)(V.W - 1), floor(mx + rr - 0.5));
+                const double y0 = fmax(0.0, ceil(my - rr - 0.5)), y1 = fmin((double)(V.H - 1), floor(my + rr - 0.5));
+                if (x0 <= x1 && y0 <= y1) {
+                    ix0 = (int32_t)x0;
+                    ix1 = (int32_t)x1;
+                    iy0 = (int32_t)y0;
+                    iy1 = (int32_t)y1;
+                    A = cam.cp / cam.det;
+                    B = -cam.bp / cam.det;
+                    Cq = cam.ap / cam.det;
+                    large = ix1 - ix0 >= kFlowSide || iy1 - iy0 >= kFlowSide;
+                    if (!large) {
+                        // q <= 9 lies inside the ellipse's box (half-extents 3 sqrt of the
+                        // covariance's diagonal, widened past every rounding)
+                        const float ex = 3.003f * sqrtf((float)cam.ap) + 0.02f, ey = 3.003f * sqrtf((float)cam.cp) + 0.02f;
+                        ix0 = max(ix0, (int32_t)ceilf((float)(mx - 0.5 - (double)ex) - 0.01f));
+                        ix1 = min(ix1, (int32_t)floorf((float)(mx - 0.5 + (double)ex) + 0.01f));
+                        iy0 = max(iy0, (int32_t)ceilf((float)(my - 0.5 - (double)ey) - 0.01f));
+                        iy1 = min(iy1, (int32_t)floorf((float)(my - 0.5 + (double)ey) + 0.01f));
+                        if (ix0 > ix1 || iy0 > iy1 || !motion_under(V, tmot, ix0, ix1, iy0, iy1, tw, th)) ix1 = ix0 - 1;
                     }
-                    found = __ballot(hit) != 0;
                 }
             }
         }
-        const int64_t sout = __shfl(out, src, 64);
-        if (found && lane == 0) dyn_gauss[sout] = 1;
+        // eight lanes per record: each takes every eighth row, from the middle out
+        __syncthreads();        // the previous step's records are done with
+        s_sq[threadIdx.x] = {mx, my, A, B, Cq, ix0, iy0, large ? ix0 - 1 : ix1, iy1};
+        __syncthreads();
+        const int32_t sub = lane % 8;
+        for (int32_t r = threadIdx.x / 8; r < kFlowThreads && base + r < count; r += kFlowThreads / 8) {
+            const Square q = s_sq[r];
+            const int32_t n = q.x1 - q.x0 + 1;
+            if (n <= 0) continue;         // culled, no motion, or left to the whole wave
+            const int32_t mid = min(max((int32_t)q.my, q.y0), q.y1);      // |mean| is finite: the square is not empty
+            const int32_t last = 2 * max(q.y1 - mid, mid - q.y0);         // rows mid, mid + 1, mid - 1, mid + 2, ...
+            const int64_t p0 = V.pix_base + q.x0;
+            bool hit = false;
+            for (int32_t k = sub; k <= last && !hit; k += 8) {
+                const int32_t y = mid + ((k & 1) ? (k + 1) / 2 : -(k / 2));
+                if (y < q.y0 || y > q.y1) continue;
+                const double dy = ((double)y + 0.5) - q.my;
+                for (int32_t o = 0; o < n && !hit; o += 16) {
+                    const int64_t p = p0 + (int64_t)y * V.W + o;
+                    uint64_t m0 = first_bytes(mask8(masks, p, n_pixels), n - o);
+                    uint64_t m1 = n - o > 8 ? first_bytes(mask8(masks, p + 8, n_pixels), n - o - 8) : 0ull;
+                    while ((m0 | m1) && !hit) {
+                        const bool lo = m0 != 0;
+                        const int32_t k8 = (int32_t)(__builtin_ctzll(lo ? m0 : m1) >> 3);
+                        const uint64_t clear = ~(0xffull << (8 * k8));
+                        if (lo) m0 &= clear; else m1 &= clear;
+                        tests++;
+                        hit = q_at(q.A, q.B, q.C, ((double)(q.x0 + o + (lo ? 0 : 8) + k8) + 0.5) - q.mx, dy) <= 9.0;
+                    }
+                }
+            }
+            if (hit) dyn_gauss[out0 + i0 + s_rec[base + r]] = 1;      // every writer stores the same value
+        }
+        // squares too large for that: all lanes on one record
+        uint64_t todo = __ballot(large);
+        while (todo) {
+            const int src = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int32_t sx0 = __shfl(ix0, src, 64), sx1 = __shfl(ix1, src, 64);
+            const int32_t sy0 = __shfl(iy0, src, 64), sy1 = __shfl(iy1, src, 64);
+            const double smx = __shfl(mx, src, 64), smy = __shfl(my, src, 64);
+            const double sA = __shfl(A, src, 64), sB = __shfl(B, src, 64), sC = __shfl(Cq, src, 64);
+            const uint8_t* M = masks + V.pix_base;
+            const int32_t per_tile = tw * th;
+            bool any = false;
+            for (int32_t ty = sy0 / th; ty <= sy1 / th && !any; ty++) {
+                for (int32_t tx = sx0 / tw; tx <= sx1 / tw && !any; tx++) {
+                    if (!tmot[V.tile_base + (int64_t)ty * V.TX + tx]) continue;
+                    for (int32_t b = 0; b < per_tile && !any; b += 64) {
+                        const int32_t p = b + lane;
+                        const int32_t x = tx * tw + p % tw, y = ty * th + p / tw;
+                        bool hit = false;
+                        if (p < per_tile && x >= sx0 && x <= sx1 && y >= sy0 && y <= sy1 && M[(int64_t)y * V.W + x]) {
+                            tests++;
+                            hit = q_at(sA, sB, sC, ((double)x + 0.5) - smx, ((double)y + 0.5) - smy) <= 9.0;
+                        }
+                        any = __ballot(hit) != 0;
+                    }
+                }
+            }
+            if (any && lane == src) dyn_gauss[out] = 1;
+        }
     }
     if (counters) {
         unsigned long long t = tests;
@@ -935,12 +1106,14 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
     const int64_t nfn = (int64_t)v->frames * v->n_gauss;
     if (nfn > 0) k_fill_u8<<<(unsigned)ceil_div(nfn, 256), 256, 0, s>>>(dyn_gauss, nfn);
     if (v->n_tiles > 0)
-        k_tile_motion<<<(unsigned)v->n_tiles, 64, 0, s>>>(v->d_views, v->n_views, v->n_tiles, v->tiling.tile_w,
-                                                          v->tiling.tile_h, masks, tile_motion);
-    if (v->n_gv > 0)
-        k_flow_mask<<<(unsigned)(v->n_views * ceil_div(v->n_gauss, 128)), 128, 0, s>>>(
-            v->d_views, v->channels, v->n_gauss, v->n_gv, v->tiling.tile_w, v->tiling.tile_h, params, masks,
-            tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
+        k_tile_motion<<<(unsigned)ceil_div(v->n_tiles, 8), 256, 0, s>>>(
+            v->d_views, v->n_views, v->n_tiles, v->n_pixels, v->tiling.tile_w, masks, tile_motion);
+    if (v->n_gv > 0) {
+        const int64_t per = ceil_div(ceil_div(v->n_gauss, kFlowRecs), 8);
+        k_flow_mask<<<(unsigned)(8 * per * v->n_views), kFlowThreads, 0, s>>>(
+            v->d_views, v->n_views, v->channels, v->n_gauss, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h, params,
+            masks, tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
+    }
     if (dyn_texel && HW > 0)
         k_dyn_texel<<<(unsigned)ceil_div(HW, 256), 256, 0, s>>>(dyn_gauss, texel_gauss, HW, v->frames, v->n_gauss,
                                                                dyn_texel);
