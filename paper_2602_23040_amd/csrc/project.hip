@@ -14,11 +14,13 @@
 // file is compiled with -ffp-contract=off), IEEE division and square root.
 // The outputs the compositing kernels read are rounded to FP32 once.
 //
-// Launch shape: one thread per Gaussian of a frame; the thread reads the
-// texel record once and loops over the views of that frame, so a batched
-// call reads the parameters once instead of once per view.  Work per
-// (Gaussian, view) is ~300 FP64 flops against 64 bytes written, so at the
-// chip's FP64 rate the kernel stays close to its HBM bound.
+// Launch shape: the threads of a Gaussian of a frame read the texel record
+// once and loop over the views of that frame, so a batched call reads the
+// parameters once instead of once per view.  Work per (Gaussian, view) is ~800
+// VALU instructions, most of them FP64, against 80 bytes written: bound by the
+// issue and the latency of its FP64 chains (50 views, 14.0 M records: 830 ->
+// 608 us with the edges facing the mean only in the tile tests, one barrier less
+// per view and the split roles; 1.9 of the 4.8 TB/s a copy reaches).
 //
 // The adjoint runs as three passes: a streaming sum of each record's
 // instance slots, the geometric chain in FP64 (position, scale, rotation,
@@ -105,8 +107,10 @@ __device__ __forceinline__ void world_chain(const float* rec, World& w) {
 #pragma unroll
     for (int r = 0; r < 3; r++)
 #pragma unroll
-        for (int k = 0; k < 3; k++)
-            w.S[3 * r + k] = (w.M[3 * r] * w.M[3 * k] + w.M[3 * r + 1] * w.M[3 * k + 1]) + w.M[3 * r + 2] * w.M[3 * k + 2];
+        for (int k = r; k < 3; k++)
+            // symmetric bit for bit: the products commute
+            w.S[3 * r + k] = w.S[3 * k + r] =
+                (w.M[3 * r] * w.M[3 * k] + w.M[3 * r + 1] * w.M[3 * k + 1]) + w.M[3 * r + 2] * w.M[3 * k + 2];
 }
 
 // Camera part of the chain.
@@ -154,10 +158,10 @@ __device__ __forceinline__ bool camera_chain(const ViewDev& V, const World& w, C
 }
 
 template <int L>
-__device__ __forceinline__ void view_dir(const ViewDev& V, const World& w, double d[3], double* dn) {
-    d[0] = w.mu[0] - V.cw[0];
-    d[1] = w.mu[1] - V.cw[1];
-    d[2] = w.mu[2] - V.cw[2];
+__device__ __forceinline__ void view_dir(const ViewDev& V, const double mu[3], double d[3], double* dn) {
+    d[0] = mu[0] - V.cw[0];
+    d[1] = mu[1] - V.cw[1];
+    d[2] = mu[2] - V.cw[2];
     *dn = sqrt((d[0] * d[0] + d[1] * d[1]) + d[2] * d[2]);
     const double inv = 1.0 / *dn;      // the direction only feeds the colour (no integer decision)
     d[0] *= inv; d[1] *= inv; d[2] *= inv;
@@ -231,73 +235,143 @@ __device__ __forceinline__ void sh_grad_dot_f(float x, float y, float z, const f
 constexpr int kMaskTiles = 64;
 constexpr double kQCull = 9.001;
 constexpr int kProjBlk = 128;
+constexpr int64_t kProjFill = 1024;     // work-groups that fill the chip
 
 __device__ __forceinline__ double q_at(double A, double B, double C, double X, double Y) {
     return (A * X * X + 2.0 * B * X * Y) + C * Y * Y;
 }
 
-// Least q over the pixel-centre rectangle [X0, X1] x [Y0, Y1] (offsets from the mean).
+// Least q over the pixel-centre rectangle [X0, X1] x [Y0, Y1] (offsets from the
+// mean).  Moving from a point towards the mean lowers q, so the least point lies
+// on an edge that faces the mean: x = Xn or y = Yn, the rectangle's nearest
+// coordinates (0 when the range holds it: the candidate then lies on the other
+// edge, or is the mean itself).  The far edges need no test.
 __device__ __forceinline__ double rect_qmin(double A, double B, double C, double ky, double kx, double X0,
                                             double X1, double Y0, double Y1) {
-    if (X0 <= 0.0 && X1 >= 0.0 && Y0 <= 0.0 && Y1 >= 0.0) return 0.0;
-    const double ya = fmin(fmax(ky * X0, Y0), Y1), yb = fmin(fmax(ky * X1, Y0), Y1);
-    const double xa = fmin(fmax(kx * Y0, X0), X1), xb = fmin(fmax(kx * Y1, X0), X1);
-    return fmin(fmin(q_at(A, B, C, X0, ya), q_at(A, B, C, X1, yb)),
-                fmin(q_at(A, B, C, xa, Y0), q_at(A, B, C, xb, Y1)));
+    const double Xn = fmin(fmax(0.0, X0), X1), Yn = fmin(fmax(0.0, Y0), Y1);
+    const double ya = fmin(fmax(ky * Xn, Y0), Y1), xb = fmin(fmax(kx * Yn, X0), X1);
+    return fmin(q_at(A, B, C, Xn, ya), q_at(A, B, C, xb, Yn));
 }
 
-// One thread per Gaussian, looping over the views of its frame.  The loop
-// runs the work-group's largest view count on every thread (threads past
-// their own count only take part in the tile tests), because each view's
-// tile tests are shared out over the work-group: rectangles range from one
-// tile to dozens, so a thread testing only its own would hold its wave for
-// the largest rectangle among 64.  Per view: every thread stages its record
-// (mean, conic, edge-vertex slopes, rectangle) in LDS; a work-group scan of
-// the rectangles' tile counts numbers the (record, tile) tests, and each
-// record writes its tests' (owner, tile) words at its place in that
-// numbering; thread t takes tests t, t + 128, ... and ORs kept tiles into
-// the owner's LDS mask.
+// Colour of a Gaussian seen along the unit direction to it, FP64; it decides no
+// integer, so its sums are fused multiply-adds.
 template <int L>
-__global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict__ views,
-                                                      const int32_t* __restrict__ frame_views,
-                                                      const int32_t* __restrict__ view_order, int32_t F, int32_t C,
-                                                      int64_t N, int32_t tw, int32_t th,
-                                                      const float* __restrict__ params,
-                                                      pg_splat* __restrict__ splats, pg_bin* __restrict__ bins,
-                                                      pg_tile_set* __restrict__ tiles,
-                                                      uint8_t* __restrict__ visible) {
+__device__ __forceinline__ void sh_color(const ViewDev& V, const double mu[3], const float* sh, float col[3]) {
     constexpr int NB = (L + 1) * (L + 1);
+    double d[3], dn;
+    view_dir<L>(V, mu, d, &dn);
+    double Y[16];
+    sh_basis<L>(d[0], d[1], d[2], Y);
+    double acc[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < NB; j++)
+#pragma unroll
+        for (int ch = 0; ch < 3; ch++) acc[ch] = fma(Y[j], (double)sh[3 * j + ch], acc[ch]);
+#pragma unroll
+    for (int ch = 0; ch < 3; ch++) {
+        const double raw = 0.5 + acc[ch];
+        col[ch] = (float)(raw > 0.0 ? raw : 0.0);
+    }
+}
+
+// One work-group per kProjBlk Gaussians of a frame, looping over the frame's
+// views (a chunk of them: see launch_project).  Each view's tile tests are
+// shared out over the work-group: rectangles range from one tile to dozens, so a
+// thread testing only its own would hold its wave for the largest rectangle
+// among 64.  Per view every geometry thread stages its record (mean, conic,
+// edge-vertex slopes, rectangle) in LDS and appends its tests' (owner, tile)
+// words to a list (in no fixed order: the tests only OR bits); then thread t
+// takes tests t, t + threads, ... and ORs kept tiles into the owner's LDS mask.
+//
+// SPLIT: the geometry and the colour run in waves of their own.  Two waves hold
+// the world chain of the Gaussians, two their SH coefficients and the FP64 basis,
+// and a view's colours cross through LDS; all four share the tile tests.  In one
+// thread the two need over 200 registers at degree 3, two waves per SIMD, and the
+// kernel waits on the latency of its FP64 chains; apart they fit 128, four waves.
+// The waves' prologues (world chain, coefficient loads) run side by side with
+// nothing to share, so it takes enough views to pay: degree 3, 293 k Gaussians
+// and 50 views 698 us together, 608 split; 410 k and 16 views 305 / 297; 410 k
+// and 10 views 202 / 206; 3.1 M and 10 views 1,200 / 1,274.
+constexpr int kSplitViews = 12;
+template <bool SPLIT>
+constexpr int proj_threads() { return SPLIT ? 2 * kProjBlk : kProjBlk; }
+
+template <int L, bool SPLIT>
+__global__ __launch_bounds__(proj_threads<SPLIT>()) __attribute__((amdgpu_waves_per_eu(SPLIT ? 4 : 1)))
+void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ frame_views,
+               const int32_t* __restrict__ view_order, int32_t C, int64_t N, int32_t tw, int32_t th,
+               const float* __restrict__ params, pg_splat* __restrict__ splats, pg_bin* __restrict__ bins,
+               pg_tile_set* __restrict__ tiles, uint8_t* __restrict__ visible) {
+    constexpr int NB = (L + 1) * (L + 1);
+    constexpr int kThreads = proj_threads<SPLIT>();
     __shared__ double s_geo[7][kProjBlk];       // mean x, y; conic A, B, C; slopes -B/C, -B/A
     __shared__ int32_t s_rect[4][kProjBlk];     // x_lo, y_lo, width, 2^16 / width rounded up
-    __shared__ uint16_t s_item[kProjBlk * kMaskTiles];   // test q: owner thread << 6 | rectangle bit
+    __shared__ uint16_t s_item[kProjBlk * kMaskTiles];   // test: owner thread << 6 | rectangle bit
     __shared__ unsigned long long s_mask[kProjBlk];
-    __shared__ int32_t s_wsum[kProjBlk / 64];
-    const int tid = threadIdx.x;
-    // grid (Gaussian chunks, frames): the frame, its views and so every view's camera
-    // are uniform over the work-group, and the camera is read with scalar loads
+    __shared__ float s_col[2][3][kProjBlk];     // colours of even and odd views of the loop (split roles)
+    __shared__ int32_t s_total[2];              // tests of even and odd views of the loop
+    const int tid = threadIdx.x, own = tid % kProjBlk;
+    // grid (Gaussian chunks, frames, view chunks): the frame, its views and so every
+    // view's camera are uniform over the work-group, and the camera is read with scalar loads
     const int32_t f = (int32_t)blockIdx.y;
-    const int64_t i0 = (int64_t)blockIdx.x * kProjBlk + tid;
-    const bool in_range = i0 < N;
-    const int64_t i = in_range ? i0 : 0;
-    const int64_t g = (int64_t)f * N + i;
-    const int32_t v0 = frame_views[f], v1 = frame_views[f + 1];
-    const int32_t nv = v1 - v0;
-    if (nv <= 0) return;     // uniform over the work-group
+    const int64_t i0 = (int64_t)blockIdx.x * kProjBlk + own;
+    const bool has = i0 < N;
+    const int64_t i = has ? i0 : 0;
+    const int32_t fv0 = frame_views[f], fv1 = frame_views[f + 1];
+    const int32_t per = (fv1 - fv0 + (int32_t)gridDim.z - 1) / (int32_t)gridDim.z;
+    const int32_t v0 = fv0 + (int32_t)blockIdx.z * per, v1 = min(fv1, v0 + per);
+    if (v0 >= v1) return;     // uniform over the work-group
     const float* P = params + (int64_t)f * C * N + i;
-    const bool has = in_range;
+    if (tid < 2) s_total[tid] = 0;
+    __syncthreads();
+    // the view's tests, by every thread; the kept tiles are in s_mask after the second barrier
+    auto tile_tests = [&](int32_t k) __attribute__((always_inline)) {
+        __syncthreads();
+        const int32_t total = s_total[k & 1];
+        if (tid == 0) s_total[(k + 1) & 1] = 0;      // last read before the previous view's second barrier
+        for (int32_t q = tid; q < total; q += kThreads) {
+            const uint32_t it = s_item[q];
+            const int32_t lo = (int32_t)(it >> 6);                 // owner
+            const int32_t bit = (int32_t)(it & 63u);               // row-major index in the rectangle
+            const int32_t row = (bit * s_rect[3][lo]) >> 16;        // bit / width (bit < 64)
+            const int32_t tx = s_rect[0][lo] + (bit - row * s_rect[2][lo]), ty = s_rect[1][lo] + row;
+            const double X0 = ((double)tx * tw + 0.5) - s_geo[0][lo], X1 = X0 + (double)(tw - 1);
+            const double Y0 = ((double)ty * th + 0.5) - s_geo[1][lo], Y1 = Y0 + (double)(th - 1);
+            const double qmin = rect_qmin(s_geo[2][lo], s_geo[3][lo], s_geo[4][lo], s_geo[5][lo], s_geo[6][lo], X0,
+                                          X1, Y0, Y1);
+            if (qmin <= kQCull) atomicOr(&s_mask[lo], 1ull << bit);
+        }
+        __syncthreads();
+    };
+    float sh[3 * NB];
+    if (SPLIT && __builtin_amdgcn_readfirstlane(tid) >= kProjBlk) {
+        // ---- colour waves
+        const double mu[3] = {P[0], P[N], P[2 * N]};
+#pragma unroll
+        for (int k = 0; k < 3 * NB; k++) sh[k] = P[(int64_t)(11 + k) * N];
+        for (int32_t vi = v0; vi < v1; vi++) {
+            const int32_t k = vi - v0;
+            float col[3];
+            sh_color<L>(views[view_order[vi]], mu, sh, col);
+#pragma unroll
+            for (int ch = 0; ch < 3; ch++) s_col[k & 1][ch][own] = col[ch];
+            tile_tests(k);
+        }
+        return;
+    }
     float rec[11];
 #pragma unroll
     for (int k = 0; k < 11; k++) rec[k] = has ? P[(int64_t)k * N] : 0.0f;
-    float sh[3 * NB];
+    if (!SPLIT) {
 #pragma unroll
-    for (int k = 0; k < 3 * NB; k++) sh[k] = has ? P[(int64_t)(11 + k) * N] : 0.0f;
+        for (int k = 0; k < 3 * NB; k++) sh[k] = P[(int64_t)(11 + k) * N];
+    }
     World w;
     world_chain(rec, w);
     const double itw = 1.0 / (double)tw, ith = 1.0 / (double)th;   // exact: tw, th are 8, 16 or 32
     bool any = false;
-    for (int32_t k = 0; k < nv; k++) {
-        const bool act = has;
-        const int32_t v = view_order[v0 + k];
+    for (int32_t vi = v0; vi < v1; vi++) {
+        const int32_t v = view_order[vi], k = vi - v0;
         const ViewDev& V = views[v];
         Cam c;
         float4 o0 = make_float4(0.f, 0.f, 0.f, 0.f), o1 = o0, o2 = o0;
@@ -305,7 +379,7 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
         int32_t nrect = 0;      // tiles of the rectangle (0: culled)
         double mx = 0.0, my = 0.0, A = 1.0, B = 0.0, Cq = 1.0;
         int32_t ixl = 0, iyl = 0, ixh = 0, iyh = 0;
-        bool ok = act && camera_chain(V, w, c) && (c.det > kDetMin);
+        const bool ok = has && camera_chain(V, w, c) && (c.det > kDetMin);
         if (ok) {
             const double tr = c.ap + c.cp;
             const double lam = 0.5 * (tr + sqrt(fmax(0.0, tr * tr - 4.0 * c.det)));
@@ -323,19 +397,12 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
             const double ylo = fmax(0.0, floor((my - rr) * ith));
             const double yhi = fmin((double)(V.TY - 1), floor((my + rr) * ith));
             const float zf = (float)c.zc;
-            double d[3], dn;
-            view_dir<L>(V, w, d, &dn);
-            double Y[16];
-            sh_basis<L>(d[0], d[1], d[2], Y);
-            float col[3];
-#pragma unroll
-            for (int ch = 0; ch < 3; ch++) {
-                double acc = 0.0;
-#pragma unroll
-                for (int j = 0; j < NB; j++) acc += Y[j] * (double)sh[3 * j + ch];
-                const double raw = 0.5 + acc;
-                col[ch] = (float)(raw > 0.0 ? raw : 0.0);
+            if (!SPLIT) {
+                float col[3];
+                sh_color<L>(V, w.mu, sh, col);
+                o2 = make_float4(col[0], col[1], col[2], 0.0f);
             }
+            o2.w = zf;
             // the conic decides no integer by itself (the tile test below keeps a
             // margin), so one reciprocal serves its three entries
             const double idet = 1.0 / c.det;
@@ -346,7 +413,6 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
             o0 = make_float4(__uint_as_float((uint32_t)bx), __uint_as_float((uint32_t)(bx >> 32)),
                              __uint_as_float((uint32_t)by), __uint_as_float((uint32_t)(by >> 32)));   // the FP64 mean's bits
             o1 = make_float4((float)A, (float)B, (float)Cq, (float)w.o);
-            o2 = make_float4(col[0], col[1], col[2], zf);
             if (xlo <= xhi && ylo <= yhi) {
                 ixl = (int32_t)xlo;
                 iyl = (int32_t)ylo;
@@ -361,45 +427,31 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
         // ---- tile tests, shared out over the work-group
         const int32_t ntest = nrect <= kMaskTiles ? nrect : 0;
         const int32_t wdt = ixh - ixl + 1;
-        s_geo[0][tid] = mx;
-        s_geo[1][tid] = my;
-        s_geo[2][tid] = A;
-        s_geo[3][tid] = B;
-        s_geo[4][tid] = Cq;
+        s_geo[0][own] = mx;
+        s_geo[1][own] = my;
+        s_geo[2][own] = A;
+        s_geo[3][own] = B;
+        s_geo[4][own] = Cq;
         const double iac = 1.0 / (A * Cq);         // edge-vertex slopes -B / C and -B / A
-        s_geo[5][tid] = -B * A * iac;
-        s_geo[6][tid] = -B * Cq * iac;
-        s_rect[0][tid] = ixl;
-        s_rect[1][tid] = iyl;
-        s_rect[2][tid] = wdt;
-        s_rect[3][tid] = (65536 + wdt - 1) / wdt;
-        s_mask[tid] = 0ull;
+        s_geo[5][own] = -B * A * iac;
+        s_geo[6][own] = -B * Cq * iac;
+        s_rect[0][own] = ixl;
+        s_rect[1][own] = iyl;
+        s_rect[2][own] = wdt;
+        s_rect[3][own] = (65536 + wdt - 1) / wdt;
+        s_mask[own] = 0ull;
         int32_t incl = ntest;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const int32_t u = __shfl_up(incl, o, 64);
             if ((tid & 63) >= o) incl += u;
         }
-        if ((tid & 63) == 63) s_wsum[tid >> 6] = incl;
-        __syncthreads();
-        if (tid >= 64) incl += s_wsum[0];
-        for (int32_t b = 0; b < ntest; b++) s_item[incl - ntest + b] = (uint16_t)((tid << 6) | b);
-        const int32_t total = s_wsum[0] + s_wsum[1];
-        __syncthreads();
-        for (int32_t q = tid; q < total; q += kProjBlk) {
-            const uint32_t it = s_item[q];
-            const int32_t lo = (int32_t)(it >> 6);                 // owner
-            const int32_t bit = (int32_t)(it & 63u);               // row-major index in the rectangle
-            const int32_t row = (bit * s_rect[3][lo]) >> 16;        // bit / width (bit < 64)
-            const int32_t tx = s_rect[0][lo] + (bit - row * s_rect[2][lo]), ty = s_rect[1][lo] + row;
-            const double X0 = ((double)tx * tw + 0.5) - s_geo[0][lo], X1 = X0 + (double)(tw - 1);
-            const double Y0 = ((double)ty * th + 0.5) - s_geo[1][lo], Y1 = Y0 + (double)(th - 1);
-            const double qmin = rect_qmin(s_geo[2][lo], s_geo[3][lo], s_geo[4][lo], s_geo[5][lo], s_geo[6][lo], X0,
-                                          X1, Y0, Y1);
-            if (qmin <= kQCull) atomicOr(&s_mask[lo], 1ull << bit);
-        }
-        __syncthreads();
-        const uint64_t tmask = ntest ? (uint64_t)s_mask[tid] : 0ull;
+        int32_t at = 0;
+        if ((tid & 63) == 63) at = atomicAdd(&s_total[k & 1], incl);      // the wave's place in the list
+        at = __builtin_amdgcn_readlane(at, 63) + incl - ntest;
+        for (int32_t b = 0; b < ntest; b++) s_item[at + b] = (uint16_t)((own << 6) | b);
+        tile_tests(k);
+        const uint64_t tmask = ntest ? (uint64_t)s_mask[own] : 0ull;
         const int32_t nt = ntest ? (int32_t)__popcll(tmask) : nrect;
         uint4 ts = make_uint4(0u, 0u, 0u, 0u);
         if (nt > 0) {
@@ -409,7 +461,12 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
         } else {
             bo = make_uint4(0u, 0u, 0u, 0u);
         }
-        if (act) {
+        if (SPLIT && ok) {
+            o2.x = s_col[k & 1][0][own];
+            o2.y = s_col[k & 1][1][own];
+            o2.z = s_col[k & 1][2][own];
+        }
+        if (has) {
             const int64_t gv = (int64_t)v * N + i;
             float4* sp = reinterpret_cast<float4*>(splats + gv);
             sp[0] = o0;
@@ -419,7 +476,7 @@ __global__ __launch_bounds__(kProjBlk) void k_project(const ViewDev* __restrict_
             reinterpret_cast<uint4*>(tiles)[gv] = ts;
         }
     }
-    if (any && has) visible[g] = 1;
+    if (any) visible[(int64_t)f * N + i] = 1;
 }
 
 // ---------------------------------------------------------------- flow masking
@@ -963,10 +1020,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_sh(const ViewDev* __restric
     if (i >= N) return;
     const int32_t v0 = frame_views[f], v1 = frame_views[f + 1];
     const float* P = params + (int64_t)f * C * N + i;
-    World wpos;                      // only mu is used (view direction)
-    wpos.mu[0] = P[0];
-    wpos.mu[1] = P[N];
-    wpos.mu[2] = P[2 * N];
+    const double mu[3] = {P[0], P[N], P[2 * N]};
     float sh[3 * NB];
 #pragma unroll
     for (int k = 0; k < 3 * NB; k++) sh[k] = P[(int64_t)(11 + k) * N];
@@ -987,7 +1041,7 @@ __global__ __launch_bounds__(128) void k_project_bwd_sh(const ViewDev* __restric
         if (gcol[0] == 0.0f && gcol[1] == 0.0f && gcol[2] == 0.0f) continue;
         const ViewDev& V = views[v];
         double dd64[3], dn64;
-        view_dir<L>(V, wpos, dd64, &dn64);
+        view_dir<L>(V, mu, dd64, &dn64);
         const float d[3] = {(float)dd64[0], (float)dd64[1], (float)dd64[2]};
         const float dn = (float)dn64;
         float Y[NB];
@@ -1124,16 +1178,24 @@ hipError_t launch_project(const pg_views* v, const float* params, pg_splat* spla
                           pg_tile_set* tiles, uint8_t* visible, hipStream_t s) {
     const int64_t n = (int64_t)v->frames * v->n_gauss;
     if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)ceil_div(v->n_gauss, 128), (unsigned)v->frames);
+    const int64_t groups = ceil_div(v->n_gauss, kProjBlk);
+    // View chunks where the Gaussians alone do not fill the chip (4,096 Gaussians in 16 views:
+    // 135 -> 14 us; 65,536 in 8 views 59 -> 29 us); with enough work-groups the world chain
+    // run once per chunk costs more than the extra ones hide (8 to 25 views per group were
+    // no faster than 50 at 2,286 groups).
+    const int64_t chunks = imin(ceil_div(kProjFill, groups * v->frames), ceil_div(v->n_views, v->frames));
+    const dim3 grid((unsigned)groups, (unsigned)v->frames, (unsigned)imax(chunks, 1));
+    const bool split = v->sh_degree >= 2 && ceil_div(v->n_views, v->frames * imax(chunks, 1)) > kSplitViews;
     auto args = [&](auto kern) {
-        kern<<<grid, 128, 0, s>>>(v->d_views, v->d_frame_views, v->d_view_order, v->frames, v->channels, v->n_gauss,
-                                  v->tiling.tile_w, v->tiling.tile_h, params, splats, bins, tiles, visible);
+        kern<<<grid, split ? proj_threads<true>() : proj_threads<false>(), 0, s>>>(
+            v->d_views, v->d_frame_views, v->d_view_order, v->channels, v->n_gauss, v->tiling.tile_w,
+            v->tiling.tile_h, params, splats, bins, tiles, visible);
     };
     switch (v->sh_degree) {
-        case 0: args(k_project<0>); break;
-        case 1: args(k_project<1>); break;
-        case 2: args(k_project<2>); break;
-        default: args(k_project<3>); break;
+        case 0: args(k_project<0, false>); break;
+        case 1: args(k_project<1, false>); break;
+        case 2: args(split ? k_project<2, true> : k_project<2, false>); break;
+        default: args(split ? k_project<3, true> : k_project<3, false>); break;
     }
     return hipGetLastError();
 }
