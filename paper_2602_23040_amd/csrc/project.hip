@@ -508,7 +508,8 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 // with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles
 // (of which the fetch, the cells and the first phase are 260).
 constexpr int kFlowThreads = 256;
-constexpr int kFlowRecs = 2048;        // Gaussians per work-group
+constexpr int kFlowRecs = 2048;        // Gaussians per work-group at most
+constexpr int64_t kFlowFill = 2048;    // work-groups that fill the chip
 constexpr int kFlowSide = 64;          // largest side of a square that eight lanes scan
 
 // Eight mask bytes from p on (zero past the end of the masks).
@@ -623,7 +624,8 @@ struct Square {
 };
 
 __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __restrict__ views, int32_t nv, int32_t C,
-                                                            int64_t N, int64_t n_pixels, int32_t tw, int32_t th,
+                                                            int64_t N, int32_t recs, int64_t n_pixels, int32_t tw,
+                                                            int32_t th,
                                                             const float* __restrict__ params,
                                                             const uint8_t* __restrict__ masks,
                                                             const uint8_t* __restrict__ tmot, uint8_t* dyn_gauss,
@@ -633,13 +635,13 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
     __shared__ int32_t s_count;
     // work-group b runs on XCD b mod 8: chunks of Gaussians are dealt to the XCDs,
     // and an XCD takes its chunks view by view
-    const int64_t chunks = ceil_div(N, kFlowRecs), per = ceil_div(chunks, 8);
+    const int64_t chunks = ceil_div(N, recs), per = ceil_div(chunks, 8);
     const int64_t j = blockIdx.x / 8, c = (int64_t)(blockIdx.x % 8) + 8 * (j % per);
     const int32_t v = (int32_t)(j / per);
     if (c >= chunks || v >= nv) return;
     const ViewDev& V = views[v];
     const int lane = (int)(threadIdx.x & 63);
-    const int64_t i0 = c * kFlowRecs;
+    const int64_t i0 = c * recs;
     const float* P0 = params + (int64_t)V.frame * C * N;
     const int64_t out0 = (int64_t)V.frame * N;
     uint64_t tests = 0;
@@ -656,7 +658,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
     }
     __syncthreads();
     // ---- phase 1
-    for (int k = threadIdx.x; k < kFlowRecs; k += kFlowThreads) {
+    for (int k = threadIdx.x; k < recs; k += kFlowThreads) {
         const int64_t i = i0 + k;
         bool keep = i < N;
         // labelled by an earlier view (a stale 0 only costs the test; with the test
@@ -1163,10 +1165,14 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
         k_tile_motion<<<(unsigned)ceil_div(v->n_tiles, 8), 256, 0, s>>>(
             v->d_views, v->n_views, v->n_tiles, v->n_pixels, v->tiling.tile_w, masks, tile_motion);
     if (v->n_gv > 0) {
-        const int64_t per = ceil_div(ceil_div(v->n_gauss, kFlowRecs), 8);
+        // Few records: smaller chunks, so that they spread over the chip (2,048 Gaussians per
+        // group / this rule: 10 views of 12,800 Gaussians 109 / 49 us, 30 of 90,000 176 / 146)
+        const int64_t want = ceil_div(v->n_gv, kFlowFill * kFlowThreads);
+        const int32_t recs = kFlowThreads * (int32_t)imin(want, kFlowRecs / kFlowThreads);
+        const int64_t per = ceil_div(ceil_div(v->n_gauss, recs), 8);
         k_flow_mask<<<(unsigned)(8 * per * v->n_views), kFlowThreads, 0, s>>>(
-            v->d_views, v->n_views, v->channels, v->n_gauss, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h, params,
-            masks, tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
+            v->d_views, v->n_views, v->channels, v->n_gauss, recs, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h,
+            params, masks, tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
     }
     if (dyn_texel && HW > 0)
         k_dyn_texel<<<(unsigned)ceil_div(HW, 256), 256, 0, s>>>(dyn_gauss, texel_gauss, HW, v->frames, v->n_gauss,

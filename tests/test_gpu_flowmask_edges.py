@@ -37,7 +37,7 @@ def masks_of(sc, kind, rng):
     (20, 61, 45, -3.0, 2, ((-1, -1, -1), (1, 1, 1))),
     (20, 7, 9, -1.5, 1, ((-1, -1, -1), (1, 1, 1))),
     (24, 200, 150, -1.0, 2, ((-1, -1, -1), (1, 1, 1))),          # squares on both sides of 64 pixels
-    (50, 128, 64, -4.5, 3, ((-1, -1, -1), (1, 1, 1))),           # 2,500 Gaussians: two work-groups per view
+    (50, 128, 64, -4.5, 3, ((-1, -1, -1), (1, 1, 1))),           # 2,500 Gaussians: ten work-groups per view
     (24, 96, 80, -3.0, 0, ((-6, -6, -0.5), (6, 6, 1.0))),        # across the near plane and outside the view
 ])
 def test_flow_mask_edges(side, w, h, lscale, views, pos, kind):
