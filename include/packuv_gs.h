@@ -452,8 +452,8 @@ pg_status pg_loss_l1_tiles(const double* tile_loss, int64_t n_tiles, int64_t n, 
 
 /* a5, second half -- Adjoint of the projection (a2) and the fetch (a1)
  * back to the texels, with gradient freezing grad <- D_i grad (Sec. 4.2
- * "Gradient Freezing").  Adds each record's instance slots in rectangle
- * order (a fixed order, so the result is bitwise deterministic), then
+ * "Gradient Freezing").  Adds each record's instance slots in a fixed order
+ * (so the result is bitwise deterministic), then
  * applies the chain rule through the EWA projection, the activations and
  * the SH colour of every view of the Gaussian's frame.
  *   splats       from pg_project: the SH adjoint takes a colour channel's clamp
