@@ -121,7 +121,8 @@ pg_status pg_views_create(const pg_camera* cams, int32_t n_views, int32_t frames
     if (n_gauss > ((int64_t)1 << 28)) return invalid("n_gauss exceeds 2^28");
     std::vector<ViewDev> hv(n_views);
     std::vector<int64_t> tb(n_views + 1), pb(n_views + 1), sb(n_views);
-    int64_t tiles = 0, pixels = 0, sblocks = 0;
+    int64_t tiles = 0, pixels = 0, sblocks = 0, photo = 0;
+    const int32_t photo_rows = photo_strip_rows(cams, n_views);
     for (int32_t v = 0; v < n_views; v++) {
         const pg_camera& c = cams[v];
         if (!(c.fx > 0.0) || !(c.fy > 0.0) || !std::isfinite(c.fx) || !std::isfinite(c.fy))
@@ -160,7 +161,8 @@ pg_status pg_views_create(const pg_camera* cams, int32_t n_views, int32_t frames
         d.pix_base = pixels;
         tb[v] = tiles;
         pb[v] = pixels;
-        sb[v] = sblocks;
+        sb[v] = photo;
+        photo += photo_groups(c.width, c.height, photo_rows);
         sblocks += (int64_t)((c.width + 31) / 32) * ((c.height + 31) / 32);
         tiles += (int64_t)d.TX * d.TY;
         pixels += (int64_t)c.width * c.height;
@@ -191,6 +193,8 @@ pg_status pg_views_create(const pg_camera* cams, int32_t n_views, int32_t frames
     p->key_bits = tile_bits;
     p->sort_passes = (32 + 7) / 8 + (tile_bits + 7) / 8;   // record (depth) passes + instance (tile) passes
     p->n_ssim_blocks = sblocks;
+    p->photo_rows = photo_rows;
+    p->n_photo = photo;
     p->h_tile_base = new int64_t[n_views + 1];
     p->h_pix_base = new int64_t[n_views + 1];
     std::memcpy(p->h_tile_base, tb.data(), sizeof(int64_t) * (n_views + 1));
@@ -199,8 +203,8 @@ pg_status pg_views_create(const pg_camera* cams, int32_t n_views, int32_t frames
     if (e == hipSuccess) e = hipMalloc(&p->d_views, sizeof(ViewDev) * n_views);
     if (e == hipSuccess) e = hipMalloc(&p->d_frame_views, sizeof(int32_t) * (frames + 1));
     if (e == hipSuccess) e = hipMalloc(&p->d_view_order, sizeof(int32_t) * n_views);
-    if (e == hipSuccess) e = hipMalloc(&p->d_ssim_base, sizeof(int64_t) * n_views);
-    if (e == hipSuccess) e = hipMemcpy(p->d_ssim_base, sb.data(), sizeof(int64_t) * n_views, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc(&p->d_photo_base, sizeof(int64_t) * n_views);
+    if (e == hipSuccess) e = hipMemcpy(p->d_photo_base, sb.data(), sizeof(int64_t) * n_views, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_views, hv.data(), sizeof(ViewDev) * n_views, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_frame_views, fv.data(), sizeof(int32_t) * (frames + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_view_order, order.data(), sizeof(int32_t) * n_views, hipMemcpyHostToDevice);
@@ -215,7 +219,7 @@ pg_status pg_views_create(const pg_camera* cams, int32_t n_views, int32_t frames
 pg_status pg_views_destroy(pg_views* v) {
     if (!v) return PG_OK;
     hipError_t e = hipSuccess;
-    for (void* d : {(void*)v->d_views, (void*)v->d_frame_views, (void*)v->d_view_order, (void*)v->d_ssim_base}) {
+    for (void* d : {(void*)v->d_views, (void*)v->d_frame_views, (void*)v->d_view_order, (void*)v->d_photo_base}) {
         if (!d) continue;
         const hipError_t r = hipFree(d);
         if (e == hipSuccess) e = r;      // free everything, report the first failure

@@ -14,16 +14,38 @@
 // partials P_a = dS/da, P_c = dS/dE[x^2], P_e = dS/dE[xy]:
 //   dS/dx_q = (w * P_a)_q + 2 x_q (w * P_c)_q + y_q (w * P_e)_q.
 //
-// One work-group of 512 threads per 32 x 32 pixel block of a view and one
-// channel at a time (the next channel's inputs load while one is computed).  Everything stays in LDS: the inputs with a 10-pixel
-// halo, their separable window sums over the 42 x 42 region the adjoint
-// needs, the three partial maps there (zero outside the view, where no S is
-// taken), and their separable blur back to the block.  The inputs are
-// shifted by the block's first pixel before squaring (E[x~^2] - a~^2 with
-// x~ = x - k equals the variance, padding included, since the window sums to
-// 1), which keeps FP32 cancellation in the variances small.  Per-block sums
-// of S and |I - T| (FP64) go to a small partial array that k_photo_final
-// reduces.
+// A wave streams down a strip of kStripCols columns of one channel, one row per
+// step, and everything between the input and the cotangent stays in registers:
+//  - the row's (x, y) goes to LDS, and each lane adds its 11 horizontal taps of x,
+//    d = x - y, d^2 and x y (four window sums instead of five: s_x + s_y - 2 s_xy
+//    is the variance of d; the products are formed per tap, since 16-byte rows
+//    of them made LDS reads the limit: 596 us against 494);
+//  - vertical windows are running sums: a new row adds its term to the ten
+//    windows under way and completes the oldest (acc[k] = acc[k + 1] + w h, one
+//    multiply-add and no shift);
+//  - the completed row's partial maps (zero outside the view, where no S is
+//    taken) go through the same two steps and give the cotangent ten rows
+//    above the input row.
+// With s_d the variance of d and m its mean, D1 = N1 + m^2 and D2 = N2 + s_d for the
+// numerators N1, N2 and denominators D1, D2 of S, so 1 - S = (N1 s_d + m^2 D2) / (D1 D2),
+// 2 P_c + P_e = P_e s_d / D2 and
+//   P_a = 2 ((N2 - N1) (a (1 - S) - m) - a S (s_d - m^2)) / (D1 D2),
+//   dS/dx_q = (w * P_a)_q + x_q (w * (2 P_c + P_e))_q - d_q (w * P_e)_q:
+// no term is a difference of large ones where the images are close, which is
+// where a fit spends its time.
+// x and y are shifted before they are multiplied (E[x~ y~] - a~ b~ with x~ = x - k
+// equals the covariance, padding included, since the window sums to 1), which
+// keeps FP32 cancellation small.  Each lane's shift is a pixel of its own column and
+// moves every kRebase rows; the windows under way are then re-expressed in the new
+// one.  (One shift for the whole strip spares 33 instructions a row and loses a
+// digit in flat areas beside texture.)  Three waves, one per channel, share a work-group; per-strip sums
+// of S and |I - T| (FP64) go to a small partial array that k_photo_final reduces.
+//
+// Bound by FP32 VALU issue, about 300 instructions per lane and row: the strip's
+// 64 lanes give 54 columns and its rows run 20 ahead of the first output, 1.3
+// times the work without halos.  The form before it (32 x 32 blocks in LDS, every
+// tap of both passes read from there) took 795 us for 16 views of 1024x768 and
+// 2,338 for 50; this one 494 and 1,273, with half the error against FP64.
 #include "pg_internal.h"
 
 namespace pg {
@@ -32,16 +54,215 @@ namespace {
 
 constexpr int kR = 5;                       // window half-width
 constexpr int kK = 2 * kR + 1;
+constexpr int kLanes = 64;
+constexpr int kStripCols = kLanes - 2 * kR; // output columns of a strip: a wave less the window's reach on both sides
+constexpr int64_t kStripFill = 1024;        // strips (of three waves) that fill the chip
+constexpr int kChannels = 3;
+constexpr int kRebase = 32;                 // rows between shifts of the base
 constexpr int kB = 32;                      // output block side
 constexpr int kIW = kB + 4 * kR;            // input patch side (42 + 10 = 52 with 2 halos)
 constexpr int kMW = kB + 2 * kR;            // partial-map region side (42)
-constexpr int kThreads = 512;              // two output pixels per thread in the last pass
+constexpr int kBlockThreads = 512;          // two output pixels per thread in the last pass
+constexpr int64_t kBlockRound = 512;        // blocks the chip takes at once (two work-groups per CU)
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
 
 struct Win {
     float w[kK];
 };
 
+__device__ __forceinline__ double wave_sum_d(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// LDS written by this wave's lanes is read by its other lanes: LDS operations of
+// a wave run in order, so only the compiler has to keep them so.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// strips: kStripCols x rows pixels of every view, numbered per view row-major
+// (ceil(W / kStripCols) x ceil(H / rows)) from strip_base[v]; a wave per channel.
+__global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per_eu(4))) void k_photo(
+    const ViewDev* __restrict__ views, int nv, const int64_t* __restrict__ strip_base, int32_t rows,
+    const float* __restrict__ image, const float* __restrict__ target, Win win, float lambda, double inv_n,
+    float* __restrict__ dimg, double* __restrict__ partial) {
+    constexpr int kIn = kLanes + 2 * kR;                     // input columns of a strip (74)
+    __shared__ float2 s_in_all[kChannels][kIn];              // x, y
+    __shared__ float4 s_map_all[kChannels][kIn];             // P_a, 2 P_c + P_e, P_e of lane l at l + kR
+    __shared__ double s_sums[kChannels][2];
+    const int64_t strip = blockIdx.x;
+    int lo = 0, hi = nv - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (strip_base[mid] <= strip) lo = mid; else hi = mid - 1;
+    }
+    const ViewDev& V = views[lo];
+    const int32_t W = V.W, H = V.H;
+    const int32_t across = (W + kStripCols - 1) / kStripCols;
+    const int64_t local = strip - strip_base[lo];
+    const int32_t xs = (int32_t)(local % across) * kStripCols;
+    const int lane = threadIdx.x % kLanes, ch = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    const int32_t y0 = (int32_t)(local / across) * rows;
+    const int32_t y1 = min(y0 + rows, H);
+    const int64_t HW = (int64_t)W * H;
+    const float* X = image + 3 * V.pix_base + ch * HW;
+    const float* Y = target + 3 * V.pix_base + ch * HW;
+    float* D = dimg + 3 * V.pix_base + ch * HW;
+    float2* s_in = s_in_all[ch];
+    float4* s_map = s_map_all[ch];
+    // lane l: input column xs - 10 + l (and, for l < 10, xs + 54 + l), map column
+    // cx = xs - 5 + l; lanes 5 .. 58 own an output column, their cx
+    const int32_t cx = xs - kR + lane;
+    const int32_t ca = xs - 2 * kR + lane, cb = ca + kLanes;
+    const bool in_a = ca >= 0 && ca < W, in_b = lane < 2 * kR && cb < W, in_map = cx >= 0 && cx < W;
+    const bool own = lane >= kR && lane < kR + kStripCols && cx < W;
+    // the next row's inputs, and the pixels whose cotangent completes there, loaded a row ahead
+    float xa = 0.f, ya = 0.f, xb = 0.f, yb = 0.f, xo = 0.f, yo = 0.f;
+    auto load_row = [&](int32_t r) __attribute__((always_inline)) {
+        if (own && r - 2 * kR >= y0 && r - 2 * kR < y1) {
+            const int64_t p = (int64_t)(r - 2 * kR) * W + cx;
+            xo = X[p];
+            yo = Y[p];
+        }
+        xa = ya = xb = yb = 0.f;
+        if (r < 0 || r >= H) return;
+        const int64_t p = (int64_t)r * W;
+        if (in_a) {
+            xa = X[p + ca];
+            ya = Y[p + ca];
+        }
+        if (in_b) {
+            xb = X[p + cb];
+            yb = Y[p + cb];
+        }
+    };
+    // running vertical windows: [k] completes after k + 1 more rows
+    float va[2 * kR], vd[2 * kR], vq[2 * kR], vr[2 * kR];      // means of x, d, x y, d^2
+    float ga[2 * kR], gf[2 * kR], ge[2 * kR];                  // blurred partial maps
+#pragma unroll
+    for (int k = 0; k < 2 * kR; k++) va[k] = vd[k] = vq[k] = vr[k] = ga[k] = gf[k] = ge[k] = 0.f;
+    // a row's term into the running windows; returns the window it completes
+    auto push = [&](float* v, float h) __attribute__((always_inline)) {
+        const float out = fmaf(win.w[2 * kR], h, v[0]);
+#pragma unroll
+        for (int k = 0; k < 2 * kR - 1; k++)
+            // three-operand form: the compiler's accumulate form leaves the sum in v[k + 1]'s register, and
+            // every row then copies all seventy windows back
+            asm("v_fma_f32 %0, %1, %2, %3" : "=v"(v[k]) : "s"(win.w[2 * kR - 1 - k]), "v"(h), "v"(v[k + 1]));
+        v[2 * kR - 1] = win.w[0] * h;
+        return out;
+    };
+    double s_sum = 0.0, l1_sum = 0.0;
+    float kx = 0.f, ky = 0.f;
+    const double w_l1 = (double)(1.0f - lambda) * inv_n, w_ssim = (double)lambda * inv_n;
+    auto rebase = [&](int32_t r) __attribute__((always_inline)) {
+        const int64_t p = (int64_t)min(max(r + kRebase / 2, 0), H - 1) * W + min(max(cx, 0), W - 1);
+        const float nx = X[p], ny = Y[p];
+        const float dx = nx - kx, dy = ny - ky;
+        // sum w (x~ - dx)(y~ - dy) = sum w x~ y~ - dx sum w y~ - dy sum w x~ + dx dy sum w
+        float wsum = 0.f;      // weights taken by window k
+#pragma unroll
+        for (int k = 2 * kR - 1; k >= 0; k--) {
+            wsum += win.w[2 * kR - 1 - k];
+            const float wx = fmaf(-kx, wsum, va[k]), wy = fmaf(-ky, wsum, va[k] - vd[k]);
+            vq[k] = fmaf(dx, fmaf(dy, wsum, -wy), fmaf(-dy, wx, vq[k]));
+        }
+        kx = nx;
+        ky = ny;
+    };
+    // input row r: the windows it completes (row r - 5)
+    float ma, md, mq, mr, xv = 0.f, yv = 0.f;
+    auto input_row = [&](int32_t r) __attribute__((always_inline)) {
+        xv = xo;
+        yv = yo;
+        s_in[lane] = make_float2(xa, ya);
+        if (lane < 2 * kR) s_in[kLanes + lane] = make_float2(xb, yb);
+        wave_lds_order();
+        load_row(r + 1);
+        float ha = 0.f, hd = 0.f, hq = 0.f, hr = 0.f;
+#pragma unroll
+        for (int j = 0; j < kK; j++) {
+            const float2 v = s_in[lane + j];
+            const float w = win.w[j], d = v.x - v.y;
+            ha = fmaf(w, v.x, ha);
+            hd = fmaf(w, d, hd);
+            hq = fmaf(w * (v.x - kx), v.y - ky, hq);
+            hr = fmaf(w, d * d, hr);
+        }
+        ma = push(va, ha);
+        md = push(vd, hd);
+        mq = push(vq, hq);
+        mr = push(vr, hr);
+    };
+    // the completed windows' S and partial maps, and the cotangent they complete (row r - 10)
+    auto output_row = [&](int32_t r) __attribute__((always_inline)) {
+        const int32_t r1 = r - kR, r2 = r - 2 * kR;
+        const bool out = own && r2 >= y0;
+        float pa = 0.f, pf = 0.f, pe = 0.f;
+        if (in_map && r1 >= 0 && r1 < H) {
+            const float a = ma, b = a - md, m2 = md * md;
+            const float sd = mr - m2, sxy = mq - (a - kx) * (b - ky);
+            const float N1 = 2.0f * a * b + kC1, N2 = 2.0f * sxy + kC2;
+            const float D1 = N1 + m2, D2 = N2 + sd;
+            const float DD = D1 * D2, rcp = __builtin_amdgcn_rcpf(DD);
+            const float iD = fmaf(rcp, fmaf(-DD, rcp, 1.0f), rcp);        // one Newton step
+            const float S = N1 * N2 * iD, U = fmaf(N1, sd, m2 * D2) * iD;     // S, 1 - S
+            pe = 2.0f * N1 * iD;
+            pf = pe * sd * (D1 * iD);
+            pa = 2.0f * iD * fmaf(N2 - N1, fmaf(a, U, -md), -(a * S) * (sd - m2));
+            if (own && r1 >= y0 && r1 < y1) s_sum += (double)S;
+        }
+        s_map[kR + lane] = make_float4(pa, pf, pe, 0.f);
+        wave_lds_order();
+        float ba = 0.f, bf = 0.f, be = 0.f;
+#pragma unroll
+        for (int j = 0; j < kK; j++) {
+            const float4 v = s_map[lane + j];              // the outer lanes' taps are not theirs; they own no column
+            const float w = win.w[j];
+            ba = fmaf(w, v.x, ba);
+            bf = fmaf(w, v.y, bf);
+            be = fmaf(w, v.z, be);
+        }
+        const float qa = push(ga, ba), qf = push(gf, bf), qe = push(ge, be);
+        if (out) {
+            const float df = xv - yv;
+            const float gs = fmaf(xv, qf, fmaf(-df, qe, qa));
+            const float sg = df > 0.f ? 1.f : (df < 0.f ? -1.f : 0.f);
+            D[(int64_t)r2 * W + cx] = (float)(w_l1 * (double)sg - w_ssim * (double)gs);
+            l1_sum += (double)fabsf(df);
+        }
+    };
+    const int32_t first = y0 - 2 * kR, last = y1 + 2 * kR;
+    load_row(first);
+    for (int32_t c0 = first; c0 < last; c0 += kRebase) {
+        rebase(c0);
+        int32_t r = c0;
+        for (; r < y0; r++) input_row(r);                  // windows of the first map row still under way
+        for (; r < min(c0 + kRebase, last); r++) {
+            input_row(r);
+            output_row(r);
+        }
+    }
+    const double ts = wave_sum_d(s_sum), tl = wave_sum_d(l1_sum);
+    if (lane == 0) {
+        s_sums[ch][0] = ts;
+        s_sums[ch][1] = tl;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        partial[2 * strip + threadIdx.x] = (s_sums[0][threadIdx.x] + s_sums[1][threadIdx.x]) + s_sums[2][threadIdx.x];
+}
+
+// ---- small tables: one work-group of 512 threads per 32 x 32 pixel block of a
+// view and one channel at a time (the next channel's inputs load while one is
+// computed).  Everything stays in LDS: the inputs with a 10-pixel halo, their
+// separable window sums over the 42 x 42 region the adjoint needs, the three
+// partial maps there, and their separable blur back to the block.  The shift is
+// the block's first pixel.
 __device__ __forceinline__ double block_sum_d(double v, double* s_w) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -51,23 +272,24 @@ __device__ __forceinline__ double block_sum_d(double v, double* s_w) {
     __syncthreads();
     double t = 0.0;
     if (threadIdx.x == 0)
-        for (int k = 0; k < kThreads / 64; k++) t += s_w[k];
+        for (int k = 0; k < kBlockThreads / 64; k++) t += s_w[k];
     return t;
 }
 
 // blocks: one per 32 x 32 block of every view, numbered per view row-major
 // (ceil(W/32) x ceil(H/32)) from blk_base[v].
-__global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ views, int nv,
-                                                    const int64_t* __restrict__ blk_base,
-                                                    const float* __restrict__ image, const float* __restrict__ target,
-                                                    Win win, float lambda, double inv_n, float* __restrict__ dimg,
-                                                    double* __restrict__ partial) {
+__global__ __launch_bounds__(kBlockThreads) void k_photo_blocks(const ViewDev* __restrict__ views, int nv,
+                                                                const int64_t* __restrict__ blk_base,
+                                                                const float* __restrict__ image,
+                                                                const float* __restrict__ target, Win win, float lambda,
+                                                                double inv_n, float* __restrict__ dimg,
+                                                                double* __restrict__ partial) {
     // LDS by lifetime: the input patch, then (over it) the partial maps; the
     // window sums, then (over them) the adjoint's horizontal blur.  65 KB, so
     // two work-groups share a CU.
     __shared__ float s_in[2 * kIW * kIW];
     __shared__ float s_h5[5 * kIW * kMW];
-    __shared__ double s_w[kThreads / 64];
+    __shared__ double s_w[kBlockThreads / 64];
     static_assert(3 * kMW * kMW <= 2 * kIW * kIW && 3 * kMW * kB <= 5 * kIW * kMW, "LDS aliasing");
     float* sx = s_in;
     float* sy = s_in + kIW * kIW;
@@ -89,14 +311,14 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
     const int t = threadIdx.x;
     double s_sum = 0.0, l1_sum = 0.0;
     // each thread's share of a channel's input patch, loaded one channel ahead
-    constexpr int kPer = (kIW * kIW + kThreads - 1) / kThreads;
+    constexpr int kPer = (kIW * kIW + kBlockThreads - 1) / kBlockThreads;
     float px[kPer], py[kPer];
     auto fetch = [&](int ch) __attribute__((always_inline)) {
         const float* X = image + 3 * V.pix_base + ch * HW;
         const float* Y = target + 3 * V.pix_base + ch * HW;
 #pragma unroll
         for (int u = 0; u < kPer; u++) {
-            const int k = t + u * kThreads;
+            const int k = t + u * kBlockThreads;
             const int gx = x0 - 2 * kR + k % kIW, gy = y0 - 2 * kR + k / kIW;
             const bool in = k < kIW * kIW && gx >= 0 && gx < V.W && gy >= 0 && gy < V.H;
             const int64_t p = (int64_t)gy * V.W + gx;
@@ -112,7 +334,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
         __syncthreads();   // the previous channel is done with the LDS
 #pragma unroll
         for (int u = 0; u < kPer; u++) {
-            const int k = t + u * kThreads;
+            const int k = t + u * kBlockThreads;
             if (k < kIW * kIW) {
                 sx[k] = px[u] - kx;
                 sy[k] = py[u] - ky;
@@ -122,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
         if (ch < 2) fetch(ch + 1);   // in flight while this channel is computed
         // horizontal window sums: input rows x partial-map columns, two adjacent
         // columns per item (12 loads per input plane for 22 taps)
-        for (int k = t; k < kIW * (kMW / 2); k += kThreads) {
+        for (int k = t; k < kIW * (kMW / 2); k += kBlockThreads) {
             const int r = k / (kMW / 2), c = 2 * (k % (kMW / 2));
             float a0 = 0.f, b0 = 0.f, c0 = 0.f, d0 = 0.f, e0 = 0.f;
             float a1 = 0.f, b1 = 0.f, c1 = 0.f, d1 = 0.f, e1 = 0.f;
@@ -158,7 +380,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
         __syncthreads();
         // vertical window sums on the partial-map region -> S and its partials,
         // two adjacent rows per item
-        for (int k = t; k < (kMW / 2) * kMW; k += kThreads) {
+        for (int k = t; k < (kMW / 2) * kMW; k += kBlockThreads) {
             const int r0 = 2 * (k / kMW), c = k % kMW;
             float m0[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, m1[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
             float prev[5];
@@ -201,7 +423,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
         __syncthreads();
         // adjoint: blur the partial maps back to the block (horizontal, then
         // vertical), two adjacent columns per item
-        for (int k = t; k < kMW * (kB / 2); k += kThreads) {
+        for (int k = t; k < kMW * (kB / 2); k += kBlockThreads) {
             const int r = k / (kB / 2), c = 2 * (k % (kB / 2));
             float a0 = 0.f, c0 = 0.f, e0 = 0.f, a1 = 0.f, c1 = 0.f, e1 = 0.f;
             float pa = sm[0][r * kMW + c], pc = sm[1][r * kMW + c], pe = sm[2][r * kMW + c];
@@ -229,7 +451,7 @@ __global__ __launch_bounds__(kThreads) void k_photo(const ViewDev* __restrict__ 
             h3[2][o + 1] = e1;
         }
         __syncthreads();
-        for (int o = t; o < kB * kB; o += kThreads) {
+        for (int o = t; o < kB * kB; o += kBlockThreads) {
             const int tx = o % kB, ty = o / kB;
             float ga = 0.f, gc = 0.f, ge = 0.f;
 #pragma unroll
@@ -406,9 +628,30 @@ hipError_t launch_regularisers(const float* params, const int64_t* n_dev, int64_
 
 int64_t photo_blocks(const pg_views* v) { return v->n_ssim_blocks; }
 
+// Rows of a strip: the tallest of 192 and 64 that gives kStripFill strips, else
+// 32 (a strip computes 20 rows more than it gives: 10 %, 31 % and 63 %; for 16
+// views of 1024x768 the three measure 484, 500 and 590 us, for one 1920x1080
+// view 260, 132 and 100).  0: the block kernel.  One round of its work-groups
+// takes 28 us, while a strip cannot be done before its 52 rows, about 56 us
+// (one view of 512x512: 28 / 56 us; four of 640x480: 89 / 79).
+int32_t photo_strip_rows(const pg_camera* cams, int32_t n_views) {
+    auto count = [&](int32_t cols, int32_t rows) {
+        int64_t n = 0;
+        for (int32_t v = 0; v < n_views; v++) n += ceil_div(cams[v].width, cols) * ceil_div(cams[v].height, rows);
+        return n;
+    };
+    if (count(kB, kB) <= kBlockRound) return 0;
+    for (int32_t rows : {192, 64})
+        if (count(kStripCols, rows) >= kStripFill) return rows;
+    return 32;
+}
+int64_t photo_groups(int32_t w, int32_t h, int32_t rows) {
+    return rows ? ceil_div(w, kStripCols) * ceil_div(h, rows) : ceil_div(w, kB) * ceil_div(h, kB);
+}
+
 hipError_t launch_photo(const pg_views* v, const float* image, const float* target, float lambda, float* dimg,
                         float* loss, double* partial, hipStream_t s) {
-    const int64_t nb = v->n_ssim_blocks;
+    const int64_t nb = v->n_photo;
     if (nb == 0 || v->n_pixels == 0) return hipSuccess;
     Win win;
     double g[kK], sum = 0.0;
@@ -419,8 +662,12 @@ hipError_t launch_photo(const pg_views* v, const float* image, const float* targ
     }
     for (int k = 0; k < kK; k++) win.w[k] = (float)(g[k] / sum);
     const double inv_n = 1.0 / (3.0 * (double)v->n_pixels);
-    k_photo<<<(unsigned)nb, kThreads, 0, s>>>(v->d_views, v->n_views, v->d_ssim_base, image, target, win, lambda,
-                                              inv_n, dimg, partial);
+    if (v->photo_rows)
+        k_photo<<<(unsigned)nb, kChannels * kLanes, 0, s>>>(v->d_views, v->n_views, v->d_photo_base, v->photo_rows,
+                                                            image, target, win, lambda, inv_n, dimg, partial);
+    else
+        k_photo_blocks<<<(unsigned)nb, kBlockThreads, 0, s>>>(v->d_views, v->n_views, v->d_photo_base, image, target,
+                                                              win, lambda, inv_n, dimg, partial);
     k_photo_final<<<1, 1024, 0, s>>>(partial, nb, lambda, inv_n, loss);
     return hipGetLastError();
 }
