@@ -77,7 +77,8 @@ struct SortWs {
     int64_t* blk_b;          // per-block tile sums in (view, id) order (slot offsets)
     int64_t* blk_b_off;
     int64_t* scan_tmp;
-    int64_t* misc;           // [0] valid records, [1] instances to sort (0 on overflow), [4] instances (slot scan)
+    int64_t* misc;           // [0] valid records, [1] instances to sort (0 on overflow), [4] instances (slot scan),
+                             // [5] the record sort's last pass moved nothing
     uint32_t* rk0;           // record sort ping-pong
     uint32_t* rk1;
     int32_t* rv0;
@@ -169,9 +170,30 @@ __device__ __forceinline__ int64_t block_sum_1024(int64_t c, int64_t* s) {
     return t;
 }
 
-__global__ __launch_bounds__(kBlk) void k_valid_count(const pg_bin* __restrict__ bins, int64_t n_gv,
-                                                      int64_t* __restrict__ blk_cnt, int64_t* __restrict__ blk_nt) {
+// What the passes of a sort count on, cleared ahead of them by an earlier kernel:
+// status words, digit counts, and the error and finished-group words after err.
+struct SortClear {
+    unsigned long long* status = nullptr;
+    int64_t status_words = 0;
+    uint32_t* hist = nullptr;
+    int32_t hist_words = 0;
+    int32_t* err = nullptr;
+    __device__ __forceinline__ void run(int64_t words, int64_t i0, int64_t stride) const {
+        for (int64_t i = i0; i < words; i += stride) status[i] = 0ull;
+        for (int64_t i = i0; i < hist_words; i += stride) hist[i] = 0u;
+            if (i0 < 2 && err) err[i0] = 0;
+    }
+};
+
+__global__ __launch_bounds__(kBlk) void k_valid_count(const pg_bin* __restrict__ bins, int64_t n_gv, int64_t n_blk,
+                                                      int64_t* __restrict__ blk_cnt, int64_t* __restrict__ blk_nt,
+                                                      SortClear clear, uint32_t* __restrict__ ranges,
+                                                      int64_t range_words) {
     __shared__ int64_t s[kBlk / 64];
+    const int64_t i0 = (int64_t)blockIdx.x * kBlk + threadIdx.x, stride = (int64_t)gridDim.x * kBlk;
+    clear.run(clear.status_words, i0, stride);
+    for (int64_t i = i0; i < range_words; i += stride) ranges[i] = 0u;
+    if (blockIdx.x >= n_blk) return;      // groups that only clear
     const int64_t gv = (int64_t)blockIdx.x * kBlk + threadIdx.x;
     const int64_t nt = gv < n_gv ? (int64_t)bins[gv].n_tiles : 0;
     const int64_t c = block_sum_1024(nt > 0 ? 1 : 0, s);
@@ -230,19 +252,7 @@ __global__ __launch_bounds__(kBlk) void k_sorted_count(const pg_tile_set* __rest
     if (threadIdx.x == 0) blk[blockIdx.x] = t;
 }
 
-// Overflow check and the next sort generation (n_inst[1], never 0: slots the
-// adjoint has not written this generation, zero-filled ones included, read
-// as zero).
-__global__ void k_post_count(int64_t* n_inst, int64_t cap, int32_t* overflow, int64_t* misc) {
-    uint32_t gen = (uint32_t)n_inst[1] + 1u;
-    n_inst[1] = (int64_t)(gen == 0u ? 1u : gen);
-    const int64_t I = *n_inst;
-    const bool of = I > cap;
-    *overflow = (*overflow & 2) | (of ? 1 : 0);
-    const int64_t eff = of ? 0 : I;
-    misc[1] = eff;
-}
-
+__global__ void k_sort_count(SortCount post) { post.finish(post.n_inst[0]); }
 
 // Emission in sorted-record order.  The group's 1024 records own consecutive
 // output ranges (their kept-tile counts scanned over the group); each thread
@@ -261,13 +271,22 @@ __device__ __forceinline__ void rect_tile(int32_t k, int32_t w, float rw, int32_
 }
 
 __global__ __launch_bounds__(kBlk) void k_emit(const uint4* __restrict__ stiles, const int32_t* __restrict__ rv_moved,
-                                               const int32_t* __restrict__ rv_stayed,
-                                               const uint32_t* __restrict__ stayed, int64_t N,
+                                               const int32_t* __restrict__ rv_stayed, int64_t N,
                                                const ViewDev* __restrict__ views,
                                                const int64_t* __restrict__ blk_off, const int64_t* __restrict__ misc,
-                                               uint32_t* __restrict__ tkeys, int32_t* __restrict__ tvals) {
-    const int32_t* __restrict__ rv = *stayed ? rv_stayed : rv_moved;   // as in k_sorted_count
+                                               uint32_t* __restrict__ tkeys, int32_t* __restrict__ tvals,
+                                               SortClear clear, int32_t passes, int32_t nb) {
+    const int32_t* __restrict__ rv = misc[5] ? rv_stayed : rv_moved;   // as in k_sorted_count
     __shared__ int32_t s_warp[kBlk / 64];
+    // the tile sort's words (its workspace overlaps the record sort's, which is done): status
+    // is [pass][tile][nb], of which the device-side count needs the first tiles
+    if (clear.err) {
+        const int64_t words = ceil_div(misc[1], kSortTile) * nb, plane = clear.status_words / passes;
+        const int64_t i0 = (int64_t)blockIdx.x * kBlk + threadIdx.x, stride = (int64_t)gridDim.x * kBlk;
+        for (int32_t q = 1; q < passes; q++)
+            for (int64_t i = i0; i < words; i += stride) clear.status[q * plane + i] = 0ull;
+        clear.run(words, i0, stride);
+    }
     if (misc[1] == 0) return;   // overflow (or nothing to emit): uniform exit
     const int t = threadIdx.x, lane = t & 63;
     const int64_t p = (int64_t)blockIdx.x * kBlk + t;
@@ -410,14 +429,56 @@ __device__ __forceinline__ uint32_t lookback_excl(unsigned long long* p, int64_t
     return excl;
 }
 
-// Digit counts of every pass of a sort in one read of the keys:
+// Exclusive scan of each pass's digit counts, a wave per pass; uni[p] = 1 when one
+// digit of pass p holds every key (the pass is then the identity permutation).
+// The counts were added at the device's coherence point and are read there.
+__device__ void os_scan(uint32_t* __restrict__ hist, int passes, int nb, int64_t n, uint32_t* __restrict__ uni) {
+    constexpr int kPer = (1 << kOsMaxBits) / 64;
+    const int lane = threadIdx.x & 63, p = threadIdx.x >> 6;
+    if (p >= passes) return;
+    const int per = nb > 64 ? nb / 64 : 1;
+    uint32_t c[kPer], sum = 0;
+    bool whole = false;
+#pragma unroll
+    for (int e = 0; e < kPer; e++) {
+        const int d = lane * per + e;
+        c[e] = e < per && d < nb ? __hip_atomic_load(&hist[p * nb + d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        whole |= n > 0 && (int64_t)c[e] == n;
+        sum += c[e];
+    }
+    const bool one = __ballot(whole) != 0;
+    if (lane == 0) uni[p] = one ? 1u : 0u;
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += u;
+    }
+    uint32_t x = incl - sum;
+#pragma unroll
+    for (int e = 0; e < kPer; e++) {
+        const int d = lane * per + e;
+        if (e < per && d < nb) hist[p * nb + d] = x;
+        x += c[e];
+    }
+}
+
+__global__ __launch_bounds__(64 * kMaxSortPasses) void k_os_scan(uint32_t* __restrict__ hist, int passes, int nb,
+                                                                const int64_t* __restrict__ n_ptr,
+                                                                uint32_t* __restrict__ uni) {
+    os_scan(hist, passes, nb, *n_ptr, uni);
+}
+
+// Digit counts of every pass of a sort in one read of the keys (and, with
+// `finished`, their scan by the last group to finish):
 // hist[p NB + d] = keys whose bits [p BITS, (p + 1) BITS) equal d.  Each wave
 // counts into its own LDS histogram; with UNIFORM, a wave whose active lanes
 // share a digit adds once (depth keys share their high bits, which would
 // otherwise serialise the LDS atomics).
 template <int BITS, bool UNIFORM>
 __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ keys, const int64_t* __restrict__ n_ptr,
-                                                 int passes, uint32_t* __restrict__ hist) {
+                                                 int passes, uint32_t* __restrict__ hist, uint32_t* __restrict__ uni,
+                                                 int32_t* __restrict__ finished) {
     constexpr int NB = 1 << BITS;
     constexpr int KPT = 16;                      // keys per thread per sweep, all loaded before they are counted
     __shared__ uint32_t s[4][kMaxSortPasses * NB];
@@ -463,37 +524,21 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
         const uint32_t c = s[0][i] + s[1][i] + s[2][i] + s[3][i];
         if (c) atomicAdd(&hist[i], c);
     }
-}
-
-// Exclusive scan of each pass's digit counts (one work-group of 512 threads);
-// uni[p] = 1 when one digit of pass p holds every key (the pass is then the
-// identity permutation).
-__global__ __launch_bounds__(512) void k_os_scan(uint32_t* __restrict__ hist, int passes, int nb,
-                                                 const int64_t* __restrict__ n_ptr, uint32_t* __restrict__ uni) {
-    __shared__ uint32_t s_w[8];
-    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    const int64_t n = *n_ptr;
-    for (int p = 0; p < passes; p++) {
-        const uint32_t c = t < nb ? hist[p * nb + t] : 0u;
-        const int all_one = __syncthreads_or(n > 0 && (int64_t)c == n);
-        if (t == 0) uni[p] = (uint32_t)all_one;
-        uint32_t incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t u = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += u;
-        }
-        if (lane == 63) s_w[wid] = incl;
-        __syncthreads();
-        uint32_t before = 0;
-        for (int w = 0; w < wid; w++) before += s_w[w];
-        if (t < nb) hist[p * nb + t] = before + incl - c;
-        __syncthreads();
-    }
+    if (!finished) return;
+    // The last group to finish turns the counts into offsets.  The counts were added by
+    // atomics at the device's coherence point, so they only have to have completed before the
+    // group reports: a device fence would also write back the whole L2 (280 us a sort at
+    // 38 M instances).
+    __shared__ int32_t s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(finished, 1) == (int32_t)gridDim.x - 1;
+    __syncthreads();
+    if (s_last) os_scan(hist, passes, NB, n, uni);
 }
 
 // Clears what the passes of one sort count on: the histograms, the look-back
-// error flag and the status words of the tiles the device-side
+// error flag, the histogram's count of finished groups (the word after it) and the status words of the tiles the device-side
 // count needs (status is [pass][tile][NB], tile stride NB, pass stride
 // tiles_max NB).
 __global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int passes, int nb, int64_t tiles_max,
@@ -506,7 +551,7 @@ __global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int passes, int nb
     for (int p = 0; p < passes; p++)
         for (int64_t i = i0; i < words; i += stride) status[p * tiles_max * nb + i] = 0ull;
     for (int64_t i = i0; i < (int64_t)passes * nb; i += stride) hist[i] = 0u;
-    if (i0 == 0) *err = 0;
+    if (i0 < 2) err[i0] = 0;
 }
 
 template <int BITS>
@@ -642,24 +687,19 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
     }
 }
 
-// Bit 1 of the caller's overflow word: some look-back gave up (results undefined).
-__global__ void k_os_report(const int32_t* __restrict__ err, int32_t* __restrict__ overflow) {
-    if (*err) *overflow |= 2;
-}
-
 // Workspace of the onesweep passes of one sort of at most `cap` pairs.
 struct OsWs {
     unsigned long long* status;
     uint32_t* hist;
     uint32_t* uni;       // per pass: one digit holds every key
-    int32_t* err;
+    int32_t* err;        // look-back error, then the histogram's finished groups
     int64_t tiles_max;
 };
 size_t os_ws_bytes(int64_t cap, DigitPlan pl) {
     const int64_t tiles = imax(ceil_div(imax(cap, 1), kSortTile), 1);
     return align256((size_t)pl.passes * tiles * ((size_t)1 << pl.digit) * 8) +
            align256((size_t)kMaxSortPasses * ((size_t)1 << kOsMaxBits) * 4) + align256(kMaxSortPasses * 4) +
-           align256(4);
+           align256(2 * 4);
 }
 OsWs os_carve(int64_t cap, DigitPlan pl, char* p) {
     OsWs w{};
@@ -675,6 +715,11 @@ OsWs os_carve(int64_t cap, DigitPlan pl, char* p) {
     return w;
 }
 
+SortClear sort_clear(const OsWs& w, DigitPlan pl) {
+    const int nb = 1 << pl.digit;
+    return {w.status, (int64_t)pl.passes * w.tiles_max * nb, w.hist, pl.passes * nb, w.err};
+}
+
 // Stable LSD sort of the *n_ptr (<= cap) pairs in (ka, va) by their low
 // pl.passes * pl.digit key bits, ping-ponging with (kb, vb); the result
 // lands in (ka, va) for an even number of passes, else in (kb, vb).
@@ -683,22 +728,22 @@ OsWs os_carve(int64_t cap, DigitPlan pl, char* p) {
 // value for every key, that pass moves nothing and the result stays where the
 // pass before left it; w.uni[passes - 1] tells the caller which.
 hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, int32_t* vb, const int64_t* n_ptr,
-                         int64_t cap, OsWs w, int32_t* overflow, bool uniform_high, bool last_may_stay,
-                         hipStream_t s) {
+                         int64_t cap, OsWs w, bool uniform_high, bool last_may_stay, bool few, hipStream_t s) {
     const int nb = 1 << pl.digit;
-    k_os_clear<<<1024, 256, 0, s>>>(n_ptr, pl.passes, nb, w.tiles_max, w.status, w.hist, w.err);
+    int32_t* finished = few ? w.err + 1 : nullptr;
+    if (!few) k_os_clear<<<1024, 256, 0, s>>>(n_ptr, pl.passes, nb, w.tiles_max, w.status, w.hist, w.err);
     const unsigned hgrid = (unsigned)imax(1, imin(2048, ceil_div(imax(cap, 1), 256 * 16)));
     switch (pl.digit) {
 #define PG_HIST(B)                                                                                     \
     case B:                                                                                            \
-        if (uniform_high) k_os_hist<B, true><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist);      \
-        else k_os_hist<B, false><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist);                  \
+        if (uniform_high) k_os_hist<B, true><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished); \
+        else k_os_hist<B, false><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished);             \
         break;
         PG_HIST(1) PG_HIST(2) PG_HIST(3) PG_HIST(4) PG_HIST(5) PG_HIST(6) PG_HIST(7) PG_HIST(8) PG_HIST(9)
 #undef PG_HIST
         default: return hipErrorInvalidValue;
     }
-    k_os_scan<<<1, 512, 0, s>>>(w.hist, pl.passes, nb, n_ptr, w.uni);
+    if (!few) k_os_scan<<<1, 64 * kMaxSortPasses, 0, s>>>(w.hist, pl.passes, nb, n_ptr, w.uni);
     const unsigned grid = (unsigned)w.tiles_max;
     for (int p = 0; p < pl.passes; p++) {
         unsigned long long* st = w.status + (int64_t)p * w.tiles_max * nb;
@@ -716,7 +761,6 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
         uint32_t* tk = ka; ka = kb; kb = tk;
         int32_t* tv = va; va = vb; vb = tv;
     }
-    if (overflow) k_os_report<<<1, 1, 0, s>>>(w.err, overflow);
     return hipGetLastError();
 }
 
@@ -728,8 +772,11 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
 // last (only the first lane of a wave loads it), so every key is read once.
 constexpr int kRangeGrid = 4096;
 __global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ keys, const int64_t* __restrict__ misc,
-                                                int32_t* __restrict__ ranges) {
+                                                int32_t* __restrict__ ranges, const int32_t* __restrict__ err,
+                                                int32_t* __restrict__ overflow) {
     const int64_t I = misc[1];
+    // bit 1 of the caller's overflow word: a look-back of the tile sort gave up (results undefined)
+    if (blockIdx.x == 0 && threadIdx.x == 0 && *err) *overflow |= 2;
     const int64_t nq = (I + 3) / 4;
     for (int64_t base = (int64_t)blockIdx.x * 256; base < nq; base += (int64_t)gridDim.x * 256) {
         const int64_t i0 = 4 * (base + threadIdx.x);
@@ -898,8 +945,8 @@ size_t sort_pairs_ws_bytes(int64_t cap, int bits) {
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, const int64_t* n_dev,
                       int64_t cap, int bits, void* ws, uint32_t** out_keys, int32_t** out_vals, hipStream_t s) {
     const DigitPlan pl = digit_plan(bits, kDepthDigitBits);
-    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, os_carve(cap, pl, (char*)ws),
-                                       nullptr, true, false, s);
+    const OsWs w = os_carve(cap, pl, (char*)ws);
+    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, w, true, false, false, s);
     const bool even = pl.passes % 2 == 0;
     *out_keys = even ? keys : keys_alt;
     *out_vals = even ? vals : vals_alt;
@@ -919,55 +966,75 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     const SortPlan pl = plan_for(v);
     SortWs w = carve(v, cap, ws, nullptr);
     const int64_t nb = n_blocks(v);
-    hipError_t e = fill_u32(ranges, 0u, 2 * v->n_tiles, s);
-    if (e != hipSuccess) return e;
-    e = fill_u32(overflow_dev, 0u, 1, s);      // bit 0: capacity overflow; bit 1: a radix pass gave up waiting
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    const SortCount post{n_inst_dev, cap, overflow_dev, w.misc, nullptr, nullptr};
     if (v->n_gv == 0) {
-        e = fill_u32(w.misc, 0u, 16, s);
+        e = fill_u32(ranges, 0u, 2 * v->n_tiles, s);
         if (e != hipSuccess) return e;
         e = fill_u32(n_inst_dev, 0u, 2, s);
         if (e != hipSuccess) return e;
-        k_post_count<<<1, 1, 0, s>>>(n_inst_dev, cap, overflow_dev, w.misc);
+        k_sort_count<<<1, 1, 0, s>>>(post);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_tile_order(ranges, v->n_tiles, w.order_cnt, w.order_base, w.order_cls, tile_order, s);
     }
     // 1. compact surviving records in (view, id) order, keyed by depth; slot offsets in the same order
-    k_valid_count<<<(unsigned)nb, kBlk, 0, s>>>(bins, v->n_gv, w.blk_a, w.blk_b);
-    e = scan_i64(w.blk_a, w.blk_a_off, nullptr, 0, nb, w.misc + 0, w.scan_tmp, s);
-    if (e != hipSuccess) return e;
-    e = scan_i64(w.blk_b, w.blk_b_off, nullptr, 0, nb, w.misc + 4, w.scan_tmp, s);
+    // (the count clears the tile ranges on its way and, with few records, the record sort's
+    // words, with groups of its own when there is more to clear than the records' groups would)
+    const bool few = nb <= kScanShort;
+    const OsWs dws = os_carve(v->n_gv, pl.depth, w.os);
+    const SortClear dclear = few ? sort_clear(dws, pl.depth) : SortClear{};
+    const int64_t clear_groups = imin(ceil_div(2 * v->n_tiles + dclear.status_words, 4 * kBlk), 256);
+    k_valid_count<<<(unsigned)imax(nb, clear_groups), kBlk, 0, s>>>(bins, v->n_gv, nb, w.blk_a, w.blk_b, dclear,
+                                                                    reinterpret_cast<uint32_t*>(ranges),
+                                                                    2 * v->n_tiles);
+    if (few) {
+        e = scan_short_i64({w.blk_a, w.blk_a_off, w.misc + 0}, {w.blk_b, w.blk_b_off, w.misc + 4}, nb, {}, s);
+    } else {
+        e = scan_i64(w.blk_a, w.blk_a_off, nullptr, 0, nb, w.misc + 0, w.scan_tmp, s);
+        if (e != hipSuccess) return e;
+        e = scan_i64(w.blk_b, w.blk_b_off, nullptr, 0, nb, w.misc + 4, w.scan_tmp, s);
+    }
     if (e != hipSuccess) return e;
     k_compact<<<(unsigned)nb, kBlk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first);
     // 2. stable LSD sort of the records by depth
     // (when the last digit is one value for every key, that pass moves nothing: the
     // records stay in the buffer the pass before wrote, and its flag says so)
-    const OsWs dws = os_carve(v->n_gv, pl.depth, w.os);
-    e = onesweep_sort(pl.depth, w.rk0, w.rv0, w.rk1, w.rv1, w.misc + 0, v->n_gv, dws, overflow_dev, true, true, s);
+    e = onesweep_sort(pl.depth, w.rk0, w.rv0, w.rk1, w.rv1, w.misc + 0, v->n_gv, dws, true, true, few, s);
     if (e != hipSuccess) return e;
     const int32_t* rva = pl.depth.passes % 2 == 0 ? w.rv0 : w.rv1;
     const int32_t* rvb = pl.depth.passes % 2 == 0 ? w.rv1 : w.rv0;
     const uint32_t* stayed = dws.uni + pl.depth.passes - 1;
     // 3. instance offsets in sorted-record order; overflow check
     k_sorted_count<<<(unsigned)nb, kBlk, 0, s>>>(tiles, rva, rvb, stayed, w.misc, w.blk_a, w.stiles);
-    e = scan_i64(w.blk_a, w.blk_a_off, nullptr, 0, nb, n_inst_dev, w.scan_tmp, s);
-    if (e != hipSuccess) return e;
-    k_post_count<<<1, 1, 0, s>>>(n_inst_dev, cap, overflow_dev, w.misc);
+    SortCount count = post;
+    count.err = dws.err;
+    count.stayed = stayed;
+    if (few) {
+        e = scan_short_i64({w.blk_a, w.blk_a_off, nullptr}, {}, nb, count, s);
+        if (e != hipSuccess) return e;
+    } else {
+        e = scan_i64(w.blk_a, w.blk_a_off, nullptr, 0, nb, n_inst_dev, w.scan_tmp, s);
+        if (e != hipSuccess) return e;
+        k_sort_count<<<1, 1, 0, s>>>(count);
+    }
     // 4. emit (tile, gv) in record order into the buffer that makes the last tile pass land in the caller's arrays
     const bool even = pl.tile.passes % 2 == 0;
     uint32_t* ta = even ? keys : w.tk_alt;
     int32_t* tva = even ? values : w.tv_alt;
     uint32_t* tb = even ? w.tk_alt : keys;
     int32_t* tvb = even ? w.tv_alt : values;
-    k_emit<<<(unsigned)nb, kBlk, 0, s>>>(w.stiles, rva, rvb, stayed, v->n_gauss, v->d_views, w.blk_a_off, w.misc, ta,
-                                         tva);
-    // 5. stable LSD sort of the instances by tile id (its workspace overlaps the depth sort's, whose flag
-    // the emission has read by then)
-    e = onesweep_sort(pl.tile, ta, tva, tb, tvb, w.misc + 1, cap, os_carve(cap, pl.tile, w.os), overflow_dev, false,
-                      false, s);
+    // (and clear the tile sort's words when few: its workspace overlaps the record sort's, whose
+    // error and flag the count has taken)
+    const OsWs tws = os_carve(cap, pl.tile, w.os);
+    k_emit<<<(unsigned)nb, kBlk, 0, s>>>(w.stiles, rva, rvb, v->n_gauss, v->d_views, w.blk_a_off, w.misc, ta, tva,
+                                         few ? sort_clear(tws, pl.tile) : SortClear{}, pl.tile.passes,
+                                         1 << pl.tile.digit);
+    // 5. stable LSD sort of the instances by tile id
+    e = onesweep_sort(pl.tile, ta, tva, tb, tvb, w.misc + 1, cap, tws, false, false, few, s);
     if (e != hipSuccess) return e;
-    k_ranges<<<(unsigned)imax(1, imin(kRangeGrid, ceil_div(cap, 256))), 256, 0, s>>>(keys, w.misc, ranges);
+    k_ranges<<<(unsigned)imax(1, imin(kRangeGrid, ceil_div(cap, 256))), 256, 0, s>>>(keys, w.misc, ranges, tws.err,
+                                                                                     overflow_dev);
     return launch_tile_order(ranges, v->n_tiles, w.order_cnt, w.order_base, w.order_cls, tile_order, s);
 }
 

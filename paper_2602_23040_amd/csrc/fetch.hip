@@ -122,7 +122,8 @@ hipError_t launch_fetch(const float* atlas, const uint8_t* occ, int32_t F, int32
     p += align256(nb * 8);
     int64_t* tmp = (int64_t*)p;
     k_occ_count<<<(unsigned)nb, kThreads, 0, s>>>(occ, HW, counts);
-    hipError_t e = scan_i32_as_i64(counts, offs, nullptr, 0, nb, n_gauss_dev, tmp, s);
+    hipError_t e = nb <= kScanShort ? scan_short_i32({counts, offs, n_gauss_dev}, nb, s)
+                                    : scan_i32_as_i64(counts, offs, nullptr, 0, nb, n_gauss_dev, tmp, s);
     if (e != hipSuccess) return e;
     k_occ_ids<<<(unsigned)nb, kThreads, 0, s>>>(occ, HW, offs, n_cap, gauss_texel, texel_gauss);
     if (n_cap > 0)
