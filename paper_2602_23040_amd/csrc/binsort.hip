@@ -275,13 +275,13 @@ __global__ __launch_bounds__(kBlk) void k_emit(const uint4* __restrict__ stiles,
                                                const ViewDev* __restrict__ views,
                                                const int64_t* __restrict__ blk_off, const int64_t* __restrict__ misc,
                                                uint32_t* __restrict__ tkeys, int32_t* __restrict__ tvals,
-                                               SortClear clear, int32_t passes, int32_t nb) {
+                                               SortClear clear, int32_t passes, int32_t nb, int32_t tile) {
     const int32_t* __restrict__ rv = misc[5] ? rv_stayed : rv_moved;   // as in k_sorted_count
     __shared__ int32_t s_warp[kBlk / 64];
     // the tile sort's words (its workspace overlaps the record sort's, which is done): status
     // is [pass][tile][nb], of which the device-side count needs the first tiles
     if (clear.err) {
-        const int64_t words = ceil_div(misc[1], kSortTile) * nb, plane = clear.status_words / passes;
+        const int64_t words = ceil_div(misc[1], tile) * nb, plane = clear.status_words / passes;
         const int64_t i0 = (int64_t)blockIdx.x * kBlk + threadIdx.x, stride = (int64_t)gridDim.x * kBlk;
         for (int32_t q = 1; q < passes; q++)
             for (int64_t i = i0; i < words; i += stride) clear.status[q * plane + i] = 0ull;
@@ -475,12 +475,11 @@ __global__ __launch_bounds__(64 * kMaxSortPasses) void k_os_scan(uint32_t* __res
 // counts into its own LDS histogram; with UNIFORM, a wave whose active lanes
 // share a digit adds once (depth keys share their high bits, which would
 // otherwise serialise the LDS atomics).
-template <int BITS, bool UNIFORM>
+template <int BITS, bool UNIFORM, int KPT>
 __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ keys, const int64_t* __restrict__ n_ptr,
                                                  int passes, uint32_t* __restrict__ hist, uint32_t* __restrict__ uni,
                                                  int32_t* __restrict__ finished) {
     constexpr int NB = 1 << BITS;
-    constexpr int KPT = 16;                      // keys per thread per sweep, all loaded before they are counted
     __shared__ uint32_t s[4][kMaxSortPasses * NB];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < passes * NB; i += 256) {
@@ -541,10 +540,10 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
 // error flag, the histogram's count of finished groups (the word after it) and the status words of the tiles the device-side
 // count needs (status is [pass][tile][NB], tile stride NB, pass stride
 // tiles_max NB).
-__global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int passes, int nb, int64_t tiles_max,
+__global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int tile, int passes, int nb, int64_t tiles_max,
                            unsigned long long* __restrict__ status, uint32_t* __restrict__ hist,
                            int32_t* __restrict__ err) {
-    const int64_t ntile = imin(ceil_div(*n_ptr, kSortTile), tiles_max);
+    const int64_t ntile = imin(ceil_div(*n_ptr, tile), tiles_max);
     const int64_t words = ntile * nb;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -554,7 +553,7 @@ __global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int passes, int nb
     if (i0 < 2) err[i0] = 0;
 }
 
-template <int BITS>
+template <int BITS, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_onesweep(const uint32_t* __restrict__ keys_in,
                                                            const int32_t* __restrict__ vals_in,
                                                            uint32_t* __restrict__ keys_out,
@@ -565,14 +564,15 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
                                                            unsigned long long* __restrict__ status,
                                                            int32_t* __restrict__ err) {
     constexpr int NB = 1 << BITS;
+    constexpr int kTile = kSortThreads * ITEMS;
     constexpr int PER = NB >= kSortThreads ? NB / kSortThreads : 1;   // digits per thread
     constexpr int ACT = NB / PER;                                     // threads owning digits
     __shared__ uint32_t s_hist[4][NB];      // per-wave digit counts, then each wave's offset inside the digit
     __shared__ uint32_t s_lstart[NB];       // first position of each digit in the tile
     __shared__ int32_t s_glob[NB];          // output index of a digit's first pair, less s_lstart
     __shared__ uint32_t s_part[kSortThreads / 64];
-    __shared__ uint32_t s_keys[kSortTile];
-    __shared__ int32_t s_vals[kSortTile];
+    __shared__ uint32_t s_keys[kTile];
+    __shared__ int32_t s_vals[kTile];
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     for (int d = t; d < NB; d += kSortThreads) {
 #pragma unroll
@@ -581,29 +581,29 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
     __syncthreads();
     const int64_t n = *n_ptr;
     const int64_t b = blockIdx.x;
-    if (b >= ceil_div(n, kSortTile)) return;
+    if (b >= ceil_div(n, kTile)) return;
     if (*uniform) {     // every key has the same digit: the stable order is the input order
         if (stay) return;   // the caller reads the input buffers when this pass is uniform
-        const int64_t e = imin(n, (b + 1) * kSortTile);
-        for (int64_t i = b * kSortTile + t; i < e; i += kSortThreads) {
+        const int64_t e = imin(n, (b + 1) * kTile);
+        for (int64_t i = b * kTile + t; i < e; i += kSortThreads) {
             keys_out[i] = keys_in[i];
             vals_out[i] = vals_in[i];
         }
         return;
     }
-    uint32_t key[kSortItems];
-    int32_t val[kSortItems];
-    uint32_t rank[kSortItems];
+    uint32_t key[ITEMS];
+    int32_t val[ITEMS];
+    uint32_t rank[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kSortItems; r++) {
-        const int64_t idx = b * kSortTile + (int64_t)wid * (kSortTile / 4) + r * 64 + lane;
+    for (int r = 0; r < ITEMS; r++) {
+        const int64_t idx = b * kTile + (int64_t)wid * (kTile / 4) + r * 64 + lane;
         const bool active = idx < n;
         key[r] = active ? keys_in[idx] : 0u;
         val[r] = active ? vals_in[idx] : 0;
     }
-    const int64_t start = b * kSortTile + (int64_t)wid * (kSortTile / 4);
+    const int64_t start = b * kTile + (int64_t)wid * (kTile / 4);
 #pragma unroll
-    for (int r = 0; r < kSortItems; r++) {
+    for (int r = 0; r < ITEMS; r++) {
         const int64_t idx = start + r * 64 + lane;
         const bool active = idx < n;
         const uint32_t d = (key[r] >> shift) & (NB - 1);
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
     __syncthreads();
     // the tile's pairs in digit order in LDS (stable: waves, then rounds, then lanes)
 #pragma unroll
-    for (int r = 0; r < kSortItems; r++) {
+    for (int r = 0; r < ITEMS; r++) {
         const int64_t idx = start + r * 64 + lane;
         if (idx < n) {
             const uint32_t d = (key[r] >> shift) & (NB - 1);
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
         }
     }
     __syncthreads();
-    const int64_t tile_n = imin(kSortTile, n - b * kSortTile);
+    const int64_t tile_n = imin(kTile, n - b * kTile);
     for (int64_t i = t; i < tile_n; i += kSortThreads) {
         const uint32_t k = s_keys[i];
         const int64_t o = (int64_t)s_glob[(k >> shift) & (NB - 1)] + i;
@@ -694,16 +694,26 @@ struct OsWs {
     uint32_t* uni;       // per pass: one digit holds every key
     int32_t* err;        // look-back error, then the histogram's finished groups
     int64_t tiles_max;
+    int32_t tile;        // pairs per work-group of a pass
 };
+// Pairs per work-group of a radix pass: 4,096 keep the scattered runs long and the
+// look-back short; 1,024 spread a sort of few pairs over the chip and let a group
+// finish sooner (pg_bin_sort, 4,096 / 1,024 pairs: 10 k records 97 / 75 us, 131 k
+// 119 / 113; 524 k records and 1 M instances 158 / 196).
+constexpr int64_t kSmallSort = 1 << 18;
+constexpr int kSmallItems = 4;
+int32_t sort_tile(int64_t cap) { return kSortThreads * (cap <= kSmallSort ? kSmallItems : kSortItems); }
+
 size_t os_ws_bytes(int64_t cap, DigitPlan pl) {
-    const int64_t tiles = imax(ceil_div(imax(cap, 1), kSortTile), 1);
+    const int64_t tiles = imax(ceil_div(imax(cap, 1), sort_tile(cap)), 1);
     return align256((size_t)pl.passes * tiles * ((size_t)1 << pl.digit) * 8) +
            align256((size_t)kMaxSortPasses * ((size_t)1 << kOsMaxBits) * 4) + align256(kMaxSortPasses * 4) +
            align256(2 * 4);
 }
 OsWs os_carve(int64_t cap, DigitPlan pl, char* p) {
     OsWs w{};
-    w.tiles_max = imax(ceil_div(imax(cap, 1), kSortTile), 1);
+    w.tile = sort_tile(cap);
+    w.tiles_max = imax(ceil_div(imax(cap, 1), w.tile), 1);
     size_t off = 0;
     w.status = (unsigned long long*)(p + off);
     off += align256((size_t)pl.passes * w.tiles_max * ((size_t)1 << pl.digit) * 8);
@@ -731,16 +741,25 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
                          int64_t cap, OsWs w, bool uniform_high, bool last_may_stay, bool few, hipStream_t s) {
     const int nb = 1 << pl.digit;
     int32_t* finished = few ? w.err + 1 : nullptr;
-    if (!few) k_os_clear<<<1024, 256, 0, s>>>(n_ptr, pl.passes, nb, w.tiles_max, w.status, w.hist, w.err);
-    const unsigned hgrid = (unsigned)imax(1, imin(2048, ceil_div(imax(cap, 1), 256 * 16)));
+    if (!few) k_os_clear<<<1024, 256, 0, s>>>(n_ptr, w.tile, pl.passes, nb, w.tiles_max, w.status, w.hist, w.err);
+    const bool small = w.tile == kSortThreads * kSmallItems;
+    const unsigned hgrid = (unsigned)imax(1, imin(2048, ceil_div(imax(cap, 1), w.tile)));
     switch (pl.digit) {
-#define PG_HIST(B)                                                                                     \
-    case B:                                                                                            \
-        if (uniform_high) k_os_hist<B, true><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished); \
-        else k_os_hist<B, false><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished);             \
+#define PG_HIST_AS(B, U, K) \
+    k_os_hist<B, U, K><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished)
+#define PG_HIST(B)                                                  \
+    case B:                                                         \
+        if (uniform_high) {                                         \
+            if (small) PG_HIST_AS(B, true, kSmallItems);            \
+            else PG_HIST_AS(B, true, kSortItems);                   \
+        } else {                                                    \
+            if (small) PG_HIST_AS(B, false, kSmallItems);           \
+            else PG_HIST_AS(B, false, kSortItems);                  \
+        }                                                           \
         break;
         PG_HIST(1) PG_HIST(2) PG_HIST(3) PG_HIST(4) PG_HIST(5) PG_HIST(6) PG_HIST(7) PG_HIST(8) PG_HIST(9)
 #undef PG_HIST
+#undef PG_HIST_AS
         default: return hipErrorInvalidValue;
     }
     if (!few) k_os_scan<<<1, 64 * kMaxSortPasses, 0, s>>>(w.hist, pl.passes, nb, n_ptr, w.uni);
@@ -751,8 +770,14 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
         switch (pl.digit) {
 #define PG_PASS(B)                                                                                          \
     case B:                                                                                                 \
-        k_onesweep<B><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, p * pl.digit, w.hist + p * nb,    \
-                                                   w.uni + p, stay, st, w.err);                             \
+        if (w.tile == kSortThreads * kSmallItems)                                                           \
+            k_onesweep<B, kSmallItems><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, p * pl.digit,    \
+                                                                    w.hist + p * nb, w.uni + p, stay, st,   \
+                                                                    w.err);                                 \
+        else                                                                                                \
+            k_onesweep<B, kSortItems><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, p * pl.digit,     \
+                                                                   w.hist + p * nb, w.uni + p, stay, st,    \
+                                                                   w.err);                                  \
         break;
             PG_PASS(1) PG_PASS(2) PG_PASS(3) PG_PASS(4) PG_PASS(5) PG_PASS(6) PG_PASS(7) PG_PASS(8) PG_PASS(9)
 #undef PG_PASS
@@ -1029,7 +1054,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     const OsWs tws = os_carve(cap, pl.tile, w.os);
     k_emit<<<(unsigned)nb, kBlk, 0, s>>>(w.stiles, rva, rvb, v->n_gauss, v->d_views, w.blk_a_off, w.misc, ta, tva,
                                          few ? sort_clear(tws, pl.tile) : SortClear{}, pl.tile.passes,
-                                         1 << pl.tile.digit);
+                                         1 << pl.tile.digit, tws.tile);
     // 5. stable LSD sort of the instances by tile id
     e = onesweep_sort(pl.tile, ta, tva, tb, tvb, w.misc + 1, cap, tws, false, false, few, s);
     if (e != hipSuccess) return e;
