@@ -375,7 +375,7 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, bool active) {
 constexpr uint32_t kStAgg = 1u, kStPre = 2u;
 constexpr int kLookbackSpins = 1 << 22;      // a bound that a working chain never reaches (~1 s of polling)
 constexpr int kMaxSortPasses = 4;
-constexpr int kLookWindow = 8;               // predecessors read at once by the look-back
+constexpr int kLookWindow = 6;               // predecessors read at once by the look-back (4 to 8 alike, 16 and 2 slower)
 
 __device__ __forceinline__ void st_publish(unsigned long long* p, uint32_t flag, uint32_t value) {
     __hip_atomic_store(p, ((unsigned long long)flag << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

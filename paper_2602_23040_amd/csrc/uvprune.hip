@@ -7,10 +7,20 @@
 // pixel, the K valid Gaussians of highest opacity are kept (by the logit,
 // which orders like the opacity; ties by ascending id).
 //
-// A segmented top-K by two stable radix sorts of (key, index) pairs: first by
+// Pixel lists: the key kernel counts each pixel's Gaussians and gives each a place in
+// its pixel's list (in any order), a scan of the counts places the lists, and a
+// Gaussian's rank is the number of entries of its list that come before it.
+// That is one pass over the Gaussians instead of seven, as long as lists are
+// short.  A list of more than kUvList entries raises a flag on the device, and
+// the lists' ranks are then left to the sorts:
+//
+// a segmented top-K by two stable radix sorts of (key, index) pairs, first by
 // the opacity (largest first), then by (frame, pixel), so each pixel's run
 // comes out ordered by opacity and then id; a Gaussian's rank is its distance
-// from the start of its run.
+// from the start of its run.  Without the flag they find no pairs and each of
+// their launches ends at once (about 2 us).  Maps with more than kUvDense
+// Gaussians a pixel go to the sorts alone.  1.26 M Gaussians of two frames on a
+// 512 x 256 map: UVMEASURED.
 #include "pg_internal.h"
 
 namespace pg {
@@ -18,6 +28,8 @@ namespace pg {
 namespace {
 
 constexpr int kT = 256;
+constexpr int kUvList = 512;        // longest pixel list ranked by comparing its entries
+constexpr int64_t kUvDense = 32;    // Gaussians per pixel and frame up to which lists are tried
 
 // float -> uint32 whose ascending order is the float's descending order
 // (-0 counts as +0, as in a float comparison)
@@ -28,14 +40,19 @@ __device__ __forceinline__ uint32_t desc_key(float x) {
     return ~asc;
 }
 
-__global__ void k_uv_count(const int64_t* __restrict__ n_dev, int64_t n_cap, int32_t F, int64_t* __restrict__ cnt) {
+// cnt[0]: records; cnt[1]: records to sort (lists: none until a list is too long).
+__global__ void k_uv_count(const int64_t* __restrict__ n_dev, int64_t n_cap, int32_t F, int lists,
+                           int64_t* __restrict__ cnt) {
     cnt[0] = (int64_t)F * imin(*n_dev, n_cap);
+    cnt[1] = lists ? 0 : cnt[0];
 }
 
 __global__ __launch_bounds__(kT) void k_uv_key(const float* __restrict__ params, const int64_t* __restrict__ n_dev,
                                                int64_t n_cap, int32_t F, int32_t C, int32_t M, int32_t Nv,
                                                const int32_t* __restrict__ expected, int32_t* __restrict__ uv,
-                                               uint32_t* __restrict__ okey, int32_t* __restrict__ oval) {
+                                               uint32_t* __restrict__ okey, int32_t* __restrict__ oval,
+                                               int32_t* __restrict__ count, int32_t* __restrict__ slot,
+                                               int64_t* __restrict__ cnt) {
     const int64_t n = imin(*n_dev, n_cap);
     const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (j >= (int64_t)F * n) return;
@@ -61,6 +78,53 @@ __global__ __launch_bounds__(kT) void k_uv_key(const float* __restrict__ params,
     uv[g] = key;
     okey[j] = key >= 0 ? desc_key(P[10 * n_cap]) : 0xFFFFFFFFu;
     oval[j] = (int32_t)g;
+    if (count && key >= 0) {
+        // the Gaussian's place in its pixel's list: which one it gets does not matter
+        const int32_t at = atomicAdd(&count[(int64_t)f * M * Nv + key], 1);
+        slot[g] = at;
+        if (at >= kUvList) cnt[1] = cnt[0];      // every writer stores the same value
+    }
+}
+
+// The lists: opacity key (high) and Gaussian of every valid record at its place, so
+// that entries in ascending order are in rank order (ties by ascending id).
+__global__ __launch_bounds__(kT) void k_uv_scatter(const int64_t* __restrict__ cnt, int64_t n_cap, int32_t M,
+                                                   int32_t Nv, const uint32_t* __restrict__ okey,
+                                                   const int32_t* __restrict__ oval, const int32_t* __restrict__ uv,
+                                                   const int32_t* __restrict__ slot, const int32_t* __restrict__ start,
+                                                   uint64_t* __restrict__ list) {
+    const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (j >= cnt[0] || cnt[1]) return;
+    const int32_t g = oval[j], u = uv[g];
+    if (u < 0) return;
+    list[(int64_t)start[(g / n_cap) * M * Nv + u] + slot[g]] = (uint64_t)okey[j] << 32 | (uint32_t)g;
+}
+
+__global__ __launch_bounds__(kT) void k_uv_list_rank(const int64_t* __restrict__ cnt, int64_t n_cap, int32_t M,
+                                                     int32_t Nv, const uint32_t* __restrict__ okey,
+                                                     const int32_t* __restrict__ oval, const int32_t* __restrict__ uv,
+                                                     const int32_t* __restrict__ start,
+                                                     const uint64_t* __restrict__ list, int32_t K,
+                                                     int32_t* __restrict__ rank, uint8_t* __restrict__ keep) {
+    const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (j >= cnt[0] || cnt[1]) return;
+    const int32_t g = oval[j], u = uv[g];
+    int32_t r = -1;
+    if (u >= 0) {
+        const int64_t pix = (g / n_cap) * M * Nv + u;
+        const uint64_t mine = (uint64_t)okey[j] << 32 | (uint32_t)g;
+        const int32_t e0 = start[pix], end = start[pix + 1];
+        r = 0;
+        for (int32_t e = e0; e < end; e += 4) {         // four entries in flight
+            uint64_t x[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) x[q] = e + q < end ? list[e + q] : ~0ull;
+#pragma unroll
+            for (int q = 0; q < 4; q++) r += x[q] < mine ? 1 : 0;
+        }
+    }
+    rank[g] = r;
+    keep[g] = r >= 0 && r < K ? 1 : 0;
 }
 
 // records in opacity order -> (frame, pixel) keys; invalid ones get F M Nv
@@ -125,10 +189,10 @@ UvWs carve_uv(int64_t n_cap, int32_t F, int32_t M, int32_t Nv, void* ws, size_t*
         return q;
     };
     UvWs w{};
-    w.cnt = (int64_t*)take(8);
+    w.cnt = (int64_t*)take(16);
     w.ka = (uint32_t*)take(n * 4);
-    w.kb = (uint32_t*)take(n * 4);
     w.va = (int32_t*)take(n * 4);
+    w.kb = (uint32_t*)take(n * 4);      // kb and vb together also hold the lists' 8-byte entries
     w.vb = (int32_t*)take(n * 4);
     w.start = (int32_t*)take(((int64_t)F * M * Nv + 1) * 4);
     const int bits = imax(32, key_bits_for((int64_t)F * M * Nv + 1));
@@ -150,25 +214,43 @@ hipError_t launch_uv_prune(const float* params, const int64_t* n_dev, int64_t n_
                            void* ws, hipStream_t s) {
     UvWs w = carve_uv(n_cap, F, M, Nv, ws, nullptr);
     const int64_t n = (int64_t)F * n_cap;
-    k_uv_count<<<1, 1, 0, s>>>(n_dev, n_cap, F, w.cnt);
+    const int64_t pixels = (int64_t)F * M * Nv;
+    const bool lists = n_cap <= kUvDense * M * Nv;
+    k_uv_count<<<1, 1, 0, s>>>(n_dev, n_cap, F, lists, w.cnt);
     if (n == 0) return hipGetLastError();
     const unsigned grid = (unsigned)ceil_div(n, kT);
-    k_uv_key<<<grid, kT, 0, s>>>(params, n_dev, n_cap, F, C, M, Nv, expected, uv, w.ka, w.va);
+    hipError_t e = hipSuccess;
+    if (lists) {
+        e = fill_u32(w.start, 0u, pixels + 1, s);
+        if (e != hipSuccess) return e;
+    }
+    k_uv_key<<<grid, kT, 0, s>>>(params, n_dev, n_cap, F, C, M, Nv, expected, uv, w.ka, w.va,
+                                 lists ? w.start : nullptr, rank, w.cnt);
+    if (lists) {
+        // counts -> list starts in place (the scan's scratch is the sorts', which come later)
+        e = scan_i32(w.start, w.start, nullptr, 0, pixels + 1, nullptr, (int64_t*)w.sort_ws, s);
+        if (e != hipSuccess) return e;
+        k_uv_scatter<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, rank, w.start, (uint64_t*)w.kb);
+        k_uv_list_rank<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, w.start, (const uint64_t*)w.kb, K, rank,
+                                             keep);
+    }
+    // records to sort: all of them, or none when the lists have ranked them
+    const int64_t* left = w.cnt + 1;
     uint32_t* ok;
     int32_t* ov;
-    hipError_t e = sort_pairs(w.ka, w.va, w.kb, w.vb, w.cnt, n, 32, w.sort_ws, &ok, &ov, s);
+    e = sort_pairs(w.ka, w.va, w.kb, w.vb, left, n, 32, w.sort_ws, &ok, &ov, s);
     if (e != hipSuccess) return e;
     // the pixel keys go to the pair the opacity order does not occupy
     uint32_t* pk = ok == w.ka ? w.kb : w.ka;
     int32_t* pv = ov == w.va ? w.vb : w.va;
-    k_uv_emit<<<grid, kT, 0, s>>>(ov, w.cnt, n_cap, M, Nv, F, uv, pk, pv);
+    k_uv_emit<<<grid, kT, 0, s>>>(ov, left, n_cap, M, Nv, F, uv, pk, pv);
     const uint32_t sentinel = (uint32_t)((int64_t)F * M * Nv);
     uint32_t* sk;
     int32_t* sv;
-    e = sort_pairs(pk, pv, ok, ov, w.cnt, n, key_bits_for((int64_t)sentinel + 1), w.sort_ws, &sk, &sv, s);
+    e = sort_pairs(pk, pv, ok, ov, left, n, key_bits_for((int64_t)sentinel + 1), w.sort_ws, &sk, &sv, s);
     if (e != hipSuccess) return e;
-    k_uv_start<<<grid, kT, 0, s>>>(sk, w.cnt, w.start);
-    k_uv_rank<<<grid, kT, 0, s>>>(sk, sv, w.cnt, w.start, sentinel, K, rank, keep);
+    k_uv_start<<<grid, kT, 0, s>>>(sk, left, w.start);
+    k_uv_rank<<<grid, kT, 0, s>>>(sk, sv, left, w.start, sentinel, K, rank, keep);
     return hipGetLastError();
 }
 
