@@ -24,6 +24,7 @@ namespace pg {
 namespace {
 
 constexpr int kQThreads = 256;
+constexpr int kQItems = 4;          // values per thread whose loads are in flight together
 
 struct QuantBits {
     int32_t b[kMaxQuantChannels];
@@ -48,7 +49,19 @@ __global__ __launch_bounds__(kQThreads) void k_quant_minmax(const float* __restr
     float lo = INFINITY, hi = -INFINITY;
     for (int32_t f = 0; f < F; f++) {
         const float* row = params + ((int64_t)f * C + c) * n_cap;
-        for (int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x; i < n; i += (int64_t)kQuantBlocks * kQThreads) {
+        constexpr int64_t stride = (int64_t)kQuantBlocks * kQThreads;
+        int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x;
+        for (; i + (kQItems - 1) * stride < n; i += kQItems * stride) {
+            float v[kQItems];
+#pragma unroll
+            for (int q = 0; q < kQItems; q++) v[q] = row[i + q * stride];
+#pragma unroll
+            for (int q = 0; q < kQItems; q++) {
+                lo = fminf(lo, v[q]);
+                hi = fmaxf(hi, v[q]);
+            }
+        }
+        for (; i < n; i += stride) {
             const float v = row[i];
             lo = fminf(lo, v);
             hi = fmaxf(hi, v);
@@ -104,26 +117,36 @@ __global__ __launch_bounds__(kQThreads) void k_quant_apply(float* __restrict__ p
     const int32_t fc = blockIdx.y;
     const int c = fc % C;
     const int64_t n = imin(*n_dev, n_cap);
-    const int64_t i = (int64_t)blockIdx.x * kQThreads + threadIdx.x;
-    if (i >= n) return;
-    const int64_t e = (int64_t)fc * n_cap + i;
+    const int64_t i0 = (int64_t)blockIdx.x * kQThreads * kQItems + threadIdx.x;
+    float* row = params + (int64_t)fc * n_cap;
+    uint16_t* code = codes ? codes + (int64_t)fc * n_cap : nullptr;
     const int K = bits.b[c];
     if (K <= 0) {
-        if (codes) codes[e] = 0;
+        if (!code) return;
+        for (int q = 0; q < kQItems; q++)
+            if (i0 + q * kQThreads < n) code[i0 + q * kQThreads] = 0;
         return;
     }
     const float lo = range[2 * c], hi = range[2 * c + 1];
     const float levels = (float)((1 << K) - 1);
     const float delta = (hi - lo) / levels;
-    float k = 0.0f;
-    if (delta > 0.0f) {
-        const float d = params[e] - lo;
-        k = rintf(d / delta);
-        k = fminf(fmaxf(k, 0.0f), levels);
+    float v[kQItems];
+#pragma unroll
+    for (int q = 0; q < kQItems; q++) v[q] = i0 + q * kQThreads < n ? row[i0 + q * kQThreads] : 0.0f;
+#pragma unroll
+    for (int q = 0; q < kQItems; q++) {
+        const int64_t i = i0 + q * kQThreads;
+        if (i >= n) break;
+        float k = 0.0f;
+        if (delta > 0.0f) {
+            const float d = v[q] - lo;
+            k = rintf(d / delta);
+            k = fminf(fmaxf(k, 0.0f), levels);
+        }
+        const float step = k * delta;
+        row[i] = lo + step;
+        if (code) code[i] = (uint16_t)k;
     }
-    const float step = k * delta;
-    params[e] = lo + step;
-    if (codes) codes[e] = (uint16_t)k;
 }
 
 }  // namespace
@@ -135,7 +158,7 @@ hipError_t launch_fake_quant(float* params, const int64_t* n_dev, int64_t n_cap,
     k_quant_minmax<<<dim3(kQuantBlocks, (unsigned)C), kQThreads, 0, s>>>(params, n_dev, n_cap, F, C, qb, partial);
     k_quant_range<<<(unsigned)C, kQuantBlocks, 0, s>>>(partial, qb, range);
     if (n_cap > 0)
-        k_quant_apply<<<dim3((unsigned)ceil_div(n_cap, kQThreads), (unsigned)(F * C)), kQThreads, 0, s>>>(
+        k_quant_apply<<<dim3((unsigned)ceil_div(n_cap, kQThreads * kQItems), (unsigned)(F * C)), kQThreads, 0, s>>>(
             params, n_dev, n_cap, C, qb, range, codes);
     return hipGetLastError();
 }
