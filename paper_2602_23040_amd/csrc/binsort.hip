@@ -16,17 +16,20 @@
 // Because the second sort is stable and every tile belongs to one view, each
 // tile's list comes out ordered by (depth, id): equal depths keep the
 // compaction order, which inside one view is ascending id.  That is the order
-// of sorting (tile, depth, id) keys, with 32-bit keys in both sorts.
+// of sorting (tile, depth, id) keys, with 32-bit keys in both sorts.  Many
+// records are sorted view by view (plan_for): both sorts then run over the
+// views' runs of the arrays, in the same kernels' launches.
 //
 // Kernels (all HBM-bound):
 //   k_valid_count / k_compact   records with n_tiles > 0 -> (depth bits, gv);
 //                               inst_first[gv] = instances of all records before
 //                               gv in (view, id) order: the record's gradient
 //                               slots, one per kept tile in rectangle order
+//   k_seg_tiles                 the views' runs, when they are sorted apart
 //   radix passes (32-bit keys)  LSD, four 8-bit digits of the depth bits
 //   k_sorted_count / k_emit     tiles per sorted record -> instance offsets ->
 //                               work-group-cooperative emission (coalesced writes)
-//   radix passes (32-bit keys)  tile ids, 6-bit digits
+//   radix passes (32-bit keys)  tile ids, 5- to 7-bit digits
 //   k_ranges                    [start, end) of every tile
 //   k_order_count/_scan/_place  the compositing kernels' tile dispatch order
 // Radix passes: one histogram kernel counts every digit of the sort in one
@@ -44,6 +47,8 @@ namespace {
 
 constexpr int kBlk = 1024;           // records per compaction / emission work-group
 
+int64_t n_blocks(const pg_views* v) { return imax(ceil_div(v->n_gv, kBlk), 1); }
+
 struct DigitPlan {
     int passes, digit;      // LSD passes of equal width digit bits
 };
@@ -58,18 +63,60 @@ DigitPlan digit_plan(int bits, int max_bits) {
     return p;
 }
 
+// Pairs per work-group of a radix pass: 4,096 keep the scattered runs long and the
+// look-back short; 1,024 spread a sort of few pairs over the chip and let a group
+// finish sooner (pg_bin_sort, 4,096 / 1,024 pairs: 10 k records 97 / 75 us, 131 k
+// 119 / 113; 524 k records and 1 M instances 158 / 196).
+constexpr int64_t kSmallSort = 1 << 18;
+
 struct SortPlan {
     DigitPlan depth, tile;  // record sort (32-bit depth keys), instance sort (tile ids)
+    int32_t segs;           // views sorted apart, 0: all views in one sort
 };
 
-SortPlan plan_for(const pg_views* v) {
+constexpr int kMaxSegs = 1024;                   // views sorted apart: a thread of k_seg_tiles each
+constexpr int64_t kSegRecords = 1 << 19;         // records from which views are sorted apart: to save a pass
+constexpr int64_t kSegRecordsAny = 1 << 21;      // ... and with no pass to save
+
+int view_bits(const pg_views* v) {
+    int64_t most = 1;
+    for (int32_t k = 0; k < v->n_views; k++) most = imax(most, v->h_tile_base[k + 1] - v->h_tile_base[k]);
+    int bits = 1;
+    while (((int64_t)1 << bits) < most) bits++;
+    return bits;
+}
+
+// Views sorted apart: the tile ids inside one view need fewer bits than those of all
+// views (two passes of 6 bits instead of three at 50 views of 1024 x 768), and records in
+// (view, depth) order gather their tile sets from one view's array at a time.  It costs
+// the launches that small sorts fold into other kernels, and a partly filled radix tile
+// per view.  pg_bin_sort, one sort / views apart, us: 50 views x 293 k records (38 M
+// instances) 1731 / 1370, 8 x 4 frames of 1080p (78 M) 2972 / 2490, 10 x 3.1 M (65 M)
+// 3274 / 3046; 16 x 262 k 569 / 448, 12 x 65 k 219 / 198, 8 x 65 k 189 / 183, 5 x 65 k
+// 186 / 186, 3 x 65 k 156 / 170; with the passes alike, 3 x 1 M 448 / 425, 2 x 1 M
+// 420 / 425, 4 x 262 k 214 / 218, 2 x 524 k 267 / 280.
+SortPlan plan_for(const pg_views* v, int64_t cap) {
     SortPlan p;
+    p.segs = 0;
     p.depth = digit_plan(32, kDepthDigitBits);
     p.tile = digit_plan(v->key_bits, kTileDigitBits);   // ceil(log2(n_tiles)), >= 1
+    if (v->n_gv >= kSegRecords && cap > kSmallSort && v->n_gauss >= kBlk && v->n_views <= kMaxSegs) {
+        const DigitPlan apart = digit_plan(view_bits(v), kTileDigitBits);   // ... of the largest view
+        if (apart.passes < p.tile.passes || (v->n_gv >= kSegRecordsAny && v->n_views > 2)) {
+            p.segs = v->n_views;
+            p.tile = apart;
+        }
+    }
     return p;
 }
 
-size_t os_ws_bytes(int64_t cap, DigitPlan pl);
+size_t os_ws_bytes(int64_t cap, DigitPlan pl, int32_t segs = 0);
+
+// One view's pairs in a sort of views apart: a run of the arrays, its radix tiles
+// counted from tile_first over all runs, its keys less `base`.
+struct SortSeg {
+    uint32_t tile_first, start, len, base;
+};
 
 struct SortWs {
     int64_t* blk_a;          // per-block sums (compaction / emission)
@@ -86,19 +133,19 @@ struct SortWs {
     uint4* stiles;           // the records' tile sets gathered in depth order (read by the emission)
     uint32_t* tk_alt;        // tile sort ping-pong partner of the caller's arrays
     int32_t* tv_alt;
+    SortSeg* rec_seg;        // the views' records and instances, when views are sorted apart
+    SortSeg* inst_seg;
     char* os;                // radix pass state (histograms, look-back status), shared by both sorts
     int32_t* order_cnt;      // tile dispatch order: per (tile group, length class) counts
     int32_t* order_base;     // ... and their class-major exclusive scan
     int32_t* order_cls;      // ... first slot and size of each class
 };
 
-int64_t n_blocks(const pg_views* v) { return imax(ceil_div(v->n_gv, kBlk), 1); }
-
 constexpr int kOrderClasses = 64; // length classes of the tile dispatch order (four per octave)
 constexpr int kOrderBlk = 256;
 
 SortWs carve(const pg_views* v, int64_t cap, void* ws, size_t* total) {
-    const SortPlan pl = plan_for(v);
+    const SortPlan pl = plan_for(v, cap);
     SortWs w{};
     const int64_t nb = n_blocks(v);
     const int64_t ngv = imax(v->n_gv, 1);
@@ -122,7 +169,9 @@ SortWs carve(const pg_views* v, int64_t cap, void* ws, size_t* total) {
     w.stiles = (uint4*)take(ngv * 16);
     w.tk_alt = (uint32_t*)take(imax(cap, 1) * 4);
     w.tv_alt = (int32_t*)take(imax(cap, 1) * 4);
-    w.os = take(std::max(os_ws_bytes(ngv, pl.depth), os_ws_bytes(cap, pl.tile)));
+    w.rec_seg = (SortSeg*)take(pl.segs * sizeof(SortSeg));
+    w.inst_seg = (SortSeg*)take(pl.segs * sizeof(SortSeg));
+    w.os = take(std::max(os_ws_bytes(ngv, pl.depth, pl.segs), os_ws_bytes(cap, pl.tile, pl.segs)));
     const int64_t order_words = ceil_div(imax(v->n_tiles, 1), kOrderBlk) * kOrderClasses;
     w.order_cnt = (int32_t*)take(order_words * 4);
     w.order_base = (int32_t*)take(order_words * 4);
@@ -211,7 +260,9 @@ __global__ __launch_bounds__(kBlk) void k_valid_count(const pg_bin* __restrict__
 __global__ __launch_bounds__(kBlk) void k_compact(const pg_bin* __restrict__ bins, int64_t n_gv,
                                                   const int64_t* __restrict__ blk_off,
                                                   const int64_t* __restrict__ blk_nt_off, uint32_t* __restrict__ rk,
-                                                  int32_t* __restrict__ rv, int32_t* __restrict__ inst_first) {
+                                                  int32_t* __restrict__ rv, int32_t* __restrict__ inst_first,
+                                                  SortSeg* __restrict__ rec_seg, SortSeg* __restrict__ inst_seg,
+                                                  int64_t N) {
     __shared__ int32_t s_warp[kBlk / 64];
     __shared__ int64_t s_warp64[kBlk / 64];
     const int64_t gv = (int64_t)blockIdx.x * kBlk + threadIdx.x;
@@ -222,11 +273,60 @@ __global__ __launch_bounds__(kBlk) void k_compact(const pg_bin* __restrict__ bin
     const int64_t nt = valid ? (int64_t)b.w : 0;
     const int64_t nt_incl = block_incl_1024_i64(nt, s_warp64);
     if (gv < n_gv) inst_first[gv] = (int32_t)(blk_nt_off[blockIdx.x] + nt_incl - nt);
+    if (rec_seg) {      // N >= kBlk: at most one view begins in this group
+        const int64_t v = ceil_div((int64_t)blockIdx.x * kBlk, N);
+        if (gv == v * N && gv < n_gv) {
+            rec_seg[v].start = (uint32_t)(blk_off[blockIdx.x] + incl - valid);
+            inst_seg[v].start = (uint32_t)(blk_nt_off[blockIdx.x] + nt_incl - nt);
+        }
+    }
     if (valid) {
         const int64_t pos = blk_off[blockIdx.x] + incl - 1;
         rk[pos] = b.z;
         rv[pos] = (int32_t)gv;
     }
+}
+
+// The views' runs of records and instances from their starts (k_compact).
+__global__ __launch_bounds__(kMaxSegs) void k_seg_tiles(const ViewDev* __restrict__ views, int32_t n_segs,
+                                                        const int64_t* __restrict__ misc, int32_t tile,
+                                                        SortSeg* __restrict__ rec_seg,
+                                                        SortSeg* __restrict__ inst_seg) {
+    __shared__ int32_t s_warp[2][kMaxSegs / 64];
+    const int32_t v = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+        SortSeg* seg = q == 0 ? rec_seg : inst_seg;
+        uint32_t len = 0;
+        if (v < n_segs) len = (v + 1 < n_segs ? seg[v + 1].start : (uint32_t)misc[q == 0 ? 0 : 4]) - seg[v].start;
+        const int32_t nt = (int32_t)ceil_div((int64_t)len, tile);
+        const int32_t incl = block_incl_1024(nt, s_warp[q]);
+        if (v < n_segs) {
+            seg[v].tile_first = (uint32_t)(incl - nt);
+            seg[v].len = len;
+            seg[v].base = q == 0 ? 0u : (uint32_t)views[v].tile_base;
+        }
+    }
+}
+
+// The run that radix tile b belongs to (wave-uniform; -1 beyond the last one).
+__device__ __forceinline__ int32_t find_seg(const SortSeg* __restrict__ segs, int32_t n_segs, uint32_t b, int32_t tile,
+                                            SortSeg& out) {
+    const int lane = threadIdx.x & 63;
+    for (int32_t c = 0; c < n_segs; c += 64) {
+        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+        if (c + lane < n_segs) q = reinterpret_cast<const uint4*>(segs)[c + lane];
+        const uint64_t hit = __ballot(b >= q.x && b - q.x < (q.z + (uint32_t)tile - 1u) / (uint32_t)tile);
+        if (hit) {
+            const int l = __builtin_ctzll(hit);
+            out.tile_first = (uint32_t)__builtin_amdgcn_readlane((int)q.x, l);
+            out.start = (uint32_t)__builtin_amdgcn_readlane((int)q.y, l);
+            out.len = (uint32_t)__builtin_amdgcn_readlane((int)q.z, l);
+            out.base = (uint32_t)__builtin_amdgcn_readlane((int)q.w, l);
+            return c + l;
+        }
+    }
+    return -1;
 }
 
 // Tile sets gathered into depth order (one 16-byte read per record) and the
@@ -432,7 +532,8 @@ __device__ __forceinline__ uint32_t lookback_excl(unsigned long long* p, int64_t
 // Exclusive scan of each pass's digit counts, a wave per pass; uni[p] = 1 when one
 // digit of pass p holds every key (the pass is then the identity permutation).
 // The counts were added at the device's coherence point and are read there.
-__device__ void os_scan(uint32_t* __restrict__ hist, int passes, int nb, int64_t n, uint32_t* __restrict__ uni) {
+__device__ void os_scan(uint32_t* __restrict__ hist, int passes, int nb, int64_t n, uint32_t start,
+                        uint32_t* __restrict__ uni, uint32_t* __restrict__ all) {
     constexpr int kPer = (1 << kOsMaxBits) / 64;
     const int lane = threadIdx.x & 63, p = threadIdx.x >> 6;
     if (p >= passes) return;
@@ -448,13 +549,14 @@ __device__ void os_scan(uint32_t* __restrict__ hist, int passes, int nb, int64_t
     }
     const bool one = __ballot(whole) != 0;
     if (lane == 0) uni[p] = one ? 1u : 0u;
+    if (lane == 0 && all && n > 0 && !one) all[p] = 0u;
     uint32_t incl = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const uint32_t u = __shfl_up(incl, o, 64);
         if (lane >= o) incl += u;
     }
-    uint32_t x = incl - sum;
+    uint32_t x = start + incl - sum;
 #pragma unroll
     for (int e = 0; e < kPer; e++) {
         const int d = lane * per + e;
@@ -465,8 +567,12 @@ __device__ void os_scan(uint32_t* __restrict__ hist, int passes, int nb, int64_t
 
 __global__ __launch_bounds__(64 * kMaxSortPasses) void k_os_scan(uint32_t* __restrict__ hist, int passes, int nb,
                                                                 const int64_t* __restrict__ n_ptr,
+                                                                const SortSeg* __restrict__ segs,
                                                                 uint32_t* __restrict__ uni) {
-    os_scan(hist, passes, nb, *n_ptr, uni);
+    if (!segs) return os_scan(hist, passes, nb, *n_ptr, 0u, uni, nullptr);
+    const int32_t v = blockIdx.x;
+    os_scan(hist + (int64_t)v * passes * nb, passes, nb, segs[v].len, segs[v].start,
+            uni + (1 + v) * kMaxSortPasses, uni);
 }
 
 // Digit counts of every pass of a sort in one read of the keys (and, with
@@ -476,48 +582,53 @@ __global__ __launch_bounds__(64 * kMaxSortPasses) void k_os_scan(uint32_t* __res
 // share a digit adds once (depth keys share their high bits, which would
 // otherwise serialise the LDS atomics).
 template <int BITS, bool UNIFORM, int KPT>
+__device__ __forceinline__ void os_count(const uint32_t* __restrict__ keys, int64_t base, int64_t n, uint32_t key0,
+                                         int passes, uint32_t* __restrict__ sw) {
+    constexpr int NB = 1 << BITS;
+    const int lane = threadIdx.x & 63;
+    uint32_t k[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; j++) {
+        const int64_t i = base + (int64_t)j * 256 + threadIdx.x;
+        k[j] = i < n ? keys[i] - key0 : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < KPT; j++) {
+        const bool active = base + (int64_t)j * 256 + threadIdx.x < n;
+        if (!UNIFORM) {
+            if (active)
+                for (int p = 0; p < passes; p++) atomicAdd(&sw[p * NB + ((k[j] >> (p * BITS)) & (NB - 1))], 1u);
+            continue;
+        }
+        const uint64_t act = __ballot(active);
+        if (act == 0) break;
+        const int lead = __builtin_ctzll(act);
+        for (int p = 0; p < passes; p++) {
+            const uint32_t d = (k[j] >> (p * BITS)) & (NB - 1);
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, lead);
+            if (__ballot(active && d == d0) == act) {
+                if (lane == lead) atomicAdd(&sw[p * NB + d0], (uint32_t)__popcll(act));   // counts only: order-free
+            } else if (active) {
+                atomicAdd(&sw[p * NB + d], 1u);
+            }
+        }
+    }
+}
+
+template <int BITS, bool UNIFORM, int KPT>
 __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ keys, const int64_t* __restrict__ n_ptr,
                                                  int passes, uint32_t* __restrict__ hist, uint32_t* __restrict__ uni,
                                                  int32_t* __restrict__ finished) {
     constexpr int NB = 1 << BITS;
     __shared__ uint32_t s[4][kMaxSortPasses * NB];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < passes * NB; i += 256) {
 #pragma unroll
         for (int w = 0; w < 4; w++) s[w][i] = 0;
     }
     __syncthreads();
     const int64_t n = *n_ptr;
-    uint32_t* sw = s[wid];
-    for (int64_t base = (int64_t)blockIdx.x * 256 * KPT; base < n; base += (int64_t)gridDim.x * 256 * KPT) {
-        uint32_t k[KPT];
-#pragma unroll
-        for (int j = 0; j < KPT; j++) {
-            const int64_t i = base + (int64_t)j * 256 + threadIdx.x;
-            k[j] = i < n ? keys[i] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < KPT; j++) {
-            const bool active = base + (int64_t)j * 256 + threadIdx.x < n;
-            if (!UNIFORM) {
-                if (active)
-                    for (int p = 0; p < passes; p++) atomicAdd(&sw[p * NB + ((k[j] >> (p * BITS)) & (NB - 1))], 1u);
-                continue;
-            }
-            const uint64_t act = __ballot(active);
-            if (act == 0) break;
-            const int lead = __builtin_ctzll(act);
-            for (int p = 0; p < passes; p++) {
-                const uint32_t d = (k[j] >> (p * BITS)) & (NB - 1);
-                const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, lead);
-                if (__ballot(active && d == d0) == act) {
-                    if (lane == lead) atomicAdd(&sw[p * NB + d0], (uint32_t)__popcll(act));   // counts only: order-free
-                } else if (active) {
-                    atomicAdd(&sw[p * NB + d], 1u);
-                }
-            }
-        }
-    }
+    for (int64_t base = (int64_t)blockIdx.x * 256 * KPT; base < n; base += (int64_t)gridDim.x * 256 * KPT)
+        os_count<BITS, UNIFORM, KPT>(keys, base, n, 0u, passes, s[threadIdx.x >> 6]);
     __syncthreads();
     for (int i = threadIdx.x; i < passes * NB; i += 256) {
         const uint32_t c = s[0][i] + s[1][i] + s[2][i] + s[3][i];
@@ -533,7 +644,49 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
     __syncthreads();
     if (threadIdx.x == 0) s_last = atomicAdd(finished, 1) == (int32_t)gridDim.x - 1;
     __syncthreads();
-    if (s_last) os_scan(hist, passes, NB, n, uni);
+    if (s_last) os_scan(hist, passes, NB, n, 0u, uni, nullptr);
+}
+
+// The digit counts of views sorted apart, hist[(v passes + p) NB + d]: a group takes a
+// run of consecutive radix tiles and adds its counts whenever the view changes.
+template <int BITS, bool UNIFORM, int KPT>
+__global__ __launch_bounds__(256) void k_os_hist_seg(const uint32_t* __restrict__ keys,
+                                                     const int64_t* __restrict__ n_ptr,
+                                                     const SortSeg* __restrict__ segs, int32_t n_segs, int passes,
+                                                     uint32_t* __restrict__ hist) {
+    constexpr int NB = 1 << BITS;
+    constexpr int kTile = 256 * KPT;
+    __shared__ uint32_t s[4][kMaxSortPasses * NB];
+    for (int i = threadIdx.x; i < passes * NB; i += 256) {
+#pragma unroll
+        for (int w = 0; w < 4; w++) s[w][i] = 0;
+    }
+    __syncthreads();
+    if (*n_ptr == 0) return;
+    const SortSeg last = segs[n_segs - 1];
+    const uint32_t tiles = last.tile_first + (last.len + kTile - 1) / kTile;
+    const uint32_t per = (tiles + gridDim.x - 1) / gridDim.x;
+    const uint32_t b1 = min((blockIdx.x + 1) * per, tiles);
+    SortSeg seg{0u, 0u, 0u, 0u};
+    int32_t cur = -1;
+    for (uint32_t b = blockIdx.x * per; b < b1;) {
+        cur = find_seg(segs, n_segs, b, kTile, seg);
+        if (cur < 0) return;      // never with a whole table: every tile below `tiles` has its run
+        const uint32_t e = min(b1, seg.tile_first + (seg.len + kTile - 1) / kTile);
+        for (; b < e; b++)
+            os_count<BITS, UNIFORM, KPT>(keys, seg.start + (int64_t)(b - seg.tile_first) * kTile,
+                                         (int64_t)seg.start + seg.len, seg.base, passes, s[threadIdx.x >> 6]);
+        __syncthreads();
+        for (int i = threadIdx.x; i < passes * NB; i += 256) {
+            const uint32_t c = s[0][i] + s[1][i] + s[2][i] + s[3][i];
+            if (c) atomicAdd(&hist[(int64_t)cur * passes * NB + i], c);
+            if (b < b1) {
+#pragma unroll
+                for (int w = 0; w < 4; w++) s[w][i] = 0;
+            }
+        }
+        __syncthreads();
+    }
 }
 
 // Clears what the passes of one sort count on: the histograms, the look-back
@@ -542,25 +695,28 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
 // tiles_max NB).
 __global__ void k_os_clear(const int64_t* __restrict__ n_ptr, int tile, int passes, int nb, int64_t tiles_max,
                            unsigned long long* __restrict__ status, uint32_t* __restrict__ hist,
-                           int32_t* __restrict__ err) {
-    const int64_t ntile = imin(ceil_div(*n_ptr, tile), tiles_max);
+                           uint32_t* __restrict__ all, int32_t n_segs, int32_t* __restrict__ err) {
+    const int64_t ntile = imin(ceil_div(*n_ptr, tile) + n_segs, tiles_max);
     const int64_t words = ntile * nb;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int p = 0; p < passes; p++)
         for (int64_t i = i0; i < words; i += stride) status[p * tiles_max * nb + i] = 0ull;
-    for (int64_t i = i0; i < (int64_t)passes * nb; i += stride) hist[i] = 0u;
+    for (int64_t i = i0; i < (int64_t)imax(n_segs, 1) * passes * nb; i += stride) hist[i] = 0u;
+    if (i0 < kMaxSortPasses) all[i0] = 1u;
     if (i0 < 2) err[i0] = 0;
 }
 
-template <int BITS, int ITEMS>
+template <int BITS, int ITEMS, bool SEG>
 __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_onesweep(const uint32_t* __restrict__ keys_in,
                                                            const int32_t* __restrict__ vals_in,
                                                            uint32_t* __restrict__ keys_out,
                                                            int32_t* __restrict__ vals_out,
-                                                           const int64_t* __restrict__ n_ptr, int shift,
-                                                           const uint32_t* __restrict__ digit_base,
-                                                           const uint32_t* __restrict__ uniform, int stay,
+                                                           const int64_t* __restrict__ n_ptr,
+                                                           const SortSeg* __restrict__ segs, int32_t n_segs, int shift,
+                                                           const uint32_t* __restrict__ digit_base, int seg_words,
+                                                           const uint32_t* __restrict__ uniform,
+                                                           const uint32_t* __restrict__ stay,
                                                            unsigned long long* __restrict__ status,
                                                            int32_t* __restrict__ err) {
     constexpr int NB = 1 << BITS;
@@ -579,13 +735,28 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
         for (int w = 0; w < 4; w++) s_hist[w][d] = 0;
     }
     __syncthreads();
-    const int64_t n = *n_ptr;
+    int64_t n = *n_ptr;                  // end of the run
     const int64_t b = blockIdx.x;
-    if (b >= ceil_div(n, kTile)) return;
+    int64_t first = b * kTile, lb = b;   // the tile's first pair; its number in the run
+    uint32_t key0 = 0u;
+    if (SEG) {
+        if (n == 0) return;
+        SortSeg seg;
+        const int32_t v = find_seg(segs, n_segs, (uint32_t)b, kTile, seg);
+        if (v < 0) return;
+        lb = b - seg.tile_first;
+        first = seg.start + lb * kTile;
+        n = (int64_t)seg.start + seg.len;
+        key0 = seg.base;
+        digit_base += v * seg_words;
+        uniform += (1 + v) * kMaxSortPasses;
+    } else if (first >= n) {
+        return;
+    }
     if (*uniform) {     // every key has the same digit: the stable order is the input order
-        if (stay) return;   // the caller reads the input buffers when this pass is uniform
-        const int64_t e = imin(n, (b + 1) * kTile);
-        for (int64_t i = b * kTile + t; i < e; i += kSortThreads) {
+        if (stay && *stay) return;   // the caller reads the input buffers when this pass moves nothing
+        const int64_t e = imin(n, first + kTile);
+        for (int64_t i = first + t; i < e; i += kSortThreads) {
             keys_out[i] = keys_in[i];
             vals_out[i] = vals_in[i];
         }
@@ -596,17 +767,17 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
     uint32_t rank[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; r++) {
-        const int64_t idx = b * kTile + (int64_t)wid * (kTile / 4) + r * 64 + lane;
+        const int64_t idx = first + (int64_t)wid * (kTile / 4) + r * 64 + lane;
         const bool active = idx < n;
         key[r] = active ? keys_in[idx] : 0u;
         val[r] = active ? vals_in[idx] : 0;
     }
-    const int64_t start = b * kTile + (int64_t)wid * (kTile / 4);
+    const int64_t start = first + (int64_t)wid * (kTile / 4);
 #pragma unroll
     for (int r = 0; r < ITEMS; r++) {
         const int64_t idx = start + r * 64 + lane;
         const bool active = idx < n;
-        const uint32_t d = (key[r] >> shift) & (NB - 1);
+        const uint32_t d = ((key[r] - key0) >> shift) & (NB - 1);
         const uint64_t peers = match_digit<BITS>(d, active);
         const uint64_t below = peers & ((1ull << lane) - 1ull);
         const uint32_t base = s_hist[wid][d];
@@ -630,7 +801,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
             }
             tot[e] = run;
             mine += run;
-            st_publish(&status[b * NB + d], b == 0 ? kStPre : kStAgg, run);
+            st_publish(&status[b * NB + d], lb == 0 ? kStPre : kStAgg, run);
         }
     }
     // exclusive scan of the tile's digit counts -> s_lstart
@@ -658,30 +829,30 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
     for (int r = 0; r < ITEMS; r++) {
         const int64_t idx = start + r * 64 + lane;
         if (idx < n) {
-            const uint32_t d = (key[r] >> shift) & (NB - 1);
+            const uint32_t d = ((key[r] - key0) >> shift) & (NB - 1);
             const uint32_t pos = s_lstart[d] + s_hist[wid][d] + rank[r];
             s_keys[pos] = key[r];
             s_vals[pos] = val[r];
         }
     }
-    // look-back: this digit's count over the tiles before b
+    // look-back: this digit's count over the run's tiles before this one
     if (t < ACT) {
 #pragma unroll
         for (int e = 0; e < PER; e++) {
             const int d = t * PER + e;
             uint32_t excl = 0;
-            if (b > 0) {
-                excl = lookback_excl(status + d, NB, b, err);
+            if (lb > 0) {
+                excl = lookback_excl(status + (b - lb) * NB + d, NB, lb, err);
                 st_publish(&status[b * NB + d], kStPre, excl + tot[e]);
             }
             s_glob[d] = (int32_t)(digit_base[d] + excl) - (int32_t)s_lstart[d];
         }
     }
     __syncthreads();
-    const int64_t tile_n = imin(kTile, n - b * kTile);
+    const int64_t tile_n = imin(kTile, n - first);
     for (int64_t i = t; i < tile_n; i += kSortThreads) {
         const uint32_t k = s_keys[i];
-        const int64_t o = (int64_t)s_glob[(k >> shift) & (NB - 1)] + i;
+        const int64_t o = (int64_t)s_glob[((k - key0) >> shift) & (NB - 1)] + i;
         keys_out[o] = k;
         vals_out[o] = s_vals[i];
     }
@@ -691,38 +862,42 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4,
 struct OsWs {
     unsigned long long* status;
     uint32_t* hist;
-    uint32_t* uni;       // per pass: one digit holds every key
+    uint32_t* uni;       // per pass: one digit holds every key (of views apart: in each view, then per view)
     int32_t* err;        // look-back error, then the histogram's finished groups
     int64_t tiles_max;
     int32_t tile;        // pairs per work-group of a pass
+    const SortSeg* segs; // the runs of views sorted apart
+    int32_t n_segs;
 };
-// Pairs per work-group of a radix pass: 4,096 keep the scattered runs long and the
-// look-back short; 1,024 spread a sort of few pairs over the chip and let a group
-// finish sooner (pg_bin_sort, 4,096 / 1,024 pairs: 10 k records 97 / 75 us, 131 k
-// 119 / 113; 524 k records and 1 M instances 158 / 196).
-constexpr int64_t kSmallSort = 1 << 18;
 constexpr int kSmallItems = 4;
 int32_t sort_tile(int64_t cap) { return kSortThreads * (cap <= kSmallSort ? kSmallItems : kSortItems); }
 
-size_t os_ws_bytes(int64_t cap, DigitPlan pl) {
-    const int64_t tiles = imax(ceil_div(imax(cap, 1), sort_tile(cap)), 1);
-    return align256((size_t)pl.passes * tiles * ((size_t)1 << pl.digit) * 8) +
-           align256((size_t)kMaxSortPasses * ((size_t)1 << kOsMaxBits) * 4) + align256(kMaxSortPasses * 4) +
-           align256(2 * 4);
-}
-OsWs os_carve(int64_t cap, DigitPlan pl, char* p) {
+// Views apart add a partly filled tile each, and a histogram and a flag per pass each.
+OsWs os_layout(int64_t cap, DigitPlan pl, const SortSeg* segs, int32_t n_segs, char* p, size_t* bytes) {
     OsWs w{};
-    w.tile = sort_tile(cap);
-    w.tiles_max = imax(ceil_div(imax(cap, 1), w.tile), 1);
+    w.tile = n_segs ? kSortTile : sort_tile(cap);
+    w.segs = n_segs ? segs : nullptr;
+    w.n_segs = n_segs;
+    w.tiles_max = imax(ceil_div(imax(cap, 1), w.tile), 1) + n_segs;
     size_t off = 0;
     w.status = (unsigned long long*)(p + off);
     off += align256((size_t)pl.passes * w.tiles_max * ((size_t)1 << pl.digit) * 8);
     w.hist = (uint32_t*)(p + off);
-    off += align256((size_t)kMaxSortPasses * ((size_t)1 << kOsMaxBits) * 4);
+    off += align256((size_t)imax(n_segs, 1) * kMaxSortPasses * ((size_t)1 << kOsMaxBits) * 4);
     w.uni = (uint32_t*)(p + off);
-    off += align256(kMaxSortPasses * 4);
+    off += align256((size_t)(1 + n_segs) * kMaxSortPasses * 4);
     w.err = (int32_t*)(p + off);
+    off += align256(2 * 4);
+    if (bytes) *bytes = off;
     return w;
+}
+size_t os_ws_bytes(int64_t cap, DigitPlan pl, int32_t segs) {
+    size_t bytes = 0;
+    os_layout(cap, pl, nullptr, segs, nullptr, &bytes);
+    return bytes;
+}
+OsWs os_carve(int64_t cap, DigitPlan pl, char* p, const SortSeg* segs = nullptr, int32_t n_segs = 0) {
+    return os_layout(cap, pl, segs, n_segs, p, nullptr);
 }
 
 SortClear sort_clear(const OsWs& w, DigitPlan pl) {
@@ -741,15 +916,22 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
                          int64_t cap, OsWs w, bool uniform_high, bool last_may_stay, bool few, hipStream_t s) {
     const int nb = 1 << pl.digit;
     int32_t* finished = few ? w.err + 1 : nullptr;
-    if (!few) k_os_clear<<<1024, 256, 0, s>>>(n_ptr, w.tile, pl.passes, nb, w.tiles_max, w.status, w.hist, w.err);
+    if (!few)
+        k_os_clear<<<1024, 256, 0, s>>>(n_ptr, w.tile, pl.passes, nb, w.tiles_max, w.status, w.hist, w.uni, w.n_segs,
+                                        w.err);
     const bool small = w.tile == kSortThreads * kSmallItems;
     const unsigned hgrid = (unsigned)imax(1, imin(2048, ceil_div(imax(cap, 1), w.tile)));
     switch (pl.digit) {
 #define PG_HIST_AS(B, U, K) \
     k_os_hist<B, U, K><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished)
+#define PG_HIST_SEG(B, U) \
+    k_os_hist_seg<B, U, kSortItems><<<hgrid, 256, 0, s>>>(ka, n_ptr, w.segs, w.n_segs, pl.passes, w.hist)
 #define PG_HIST(B)                                                  \
     case B:                                                         \
-        if (uniform_high) {                                         \
+        if (w.n_segs) {                                             \
+            if (uniform_high) PG_HIST_SEG(B, true);                 \
+            else PG_HIST_SEG(B, false);                             \
+        } else if (uniform_high) {                                  \
             if (small) PG_HIST_AS(B, true, kSmallItems);            \
             else PG_HIST_AS(B, true, kSortItems);                   \
         } else {                                                    \
@@ -760,27 +942,30 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
         PG_HIST(1) PG_HIST(2) PG_HIST(3) PG_HIST(4) PG_HIST(5) PG_HIST(6) PG_HIST(7) PG_HIST(8) PG_HIST(9)
 #undef PG_HIST
 #undef PG_HIST_AS
+#undef PG_HIST_SEG
         default: return hipErrorInvalidValue;
     }
-    if (!few) k_os_scan<<<1, 64 * kMaxSortPasses, 0, s>>>(w.hist, pl.passes, nb, n_ptr, w.uni);
+    if (!few)
+        k_os_scan<<<(unsigned)imax(w.n_segs, 1), 64 * kMaxSortPasses, 0, s>>>(w.hist, pl.passes, nb, n_ptr, w.segs,
+                                                                              w.uni);
     const unsigned grid = (unsigned)w.tiles_max;
     for (int p = 0; p < pl.passes; p++) {
         unsigned long long* st = w.status + (int64_t)p * w.tiles_max * nb;
-        const int stay = last_may_stay && p == pl.passes - 1 ? 1 : 0;
+        const uint32_t* stay = last_may_stay && p == pl.passes - 1 ? w.uni + p : nullptr;
         switch (pl.digit) {
-#define PG_PASS(B)                                                                                          \
-    case B:                                                                                                 \
-        if (w.tile == kSortThreads * kSmallItems)                                                           \
-            k_onesweep<B, kSmallItems><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, p * pl.digit,    \
-                                                                    w.hist + p * nb, w.uni + p, stay, st,   \
-                                                                    w.err);                                 \
-        else                                                                                                \
-            k_onesweep<B, kSortItems><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, p * pl.digit,     \
-                                                                   w.hist + p * nb, w.uni + p, stay, st,    \
-                                                                   w.err);                                  \
+#define PG_PASS_AS(B, K, SEG)                                                                              \
+    k_onesweep<B, K, SEG><<<grid, kSortThreads, 0, s>>>(ka, va, kb, vb, n_ptr, w.segs, w.n_segs,            \
+                                                        p * pl.digit, w.hist + p * nb, pl.passes * nb,      \
+                                                        w.uni + p, stay, st, w.err)
+#define PG_PASS(B)                                         \
+    case B:                                                \
+        if (w.n_segs) PG_PASS_AS(B, kSortItems, true);     \
+        else if (small) PG_PASS_AS(B, kSmallItems, false); \
+        else PG_PASS_AS(B, kSortItems, false);             \
         break;
             PG_PASS(1) PG_PASS(2) PG_PASS(3) PG_PASS(4) PG_PASS(5) PG_PASS(6) PG_PASS(7) PG_PASS(8) PG_PASS(9)
 #undef PG_PASS
+#undef PG_PASS_AS
             default: return hipErrorInvalidValue;
         }
         uint32_t* tk = ka; ka = kb; kb = tk;
@@ -988,7 +1173,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
                            uint32_t* keys, int32_t* values,
                            int32_t* ranges, int32_t* tile_order, int32_t* inst_first, int64_t* n_inst_dev,
                            int32_t* overflow_dev, void* ws, hipStream_t s) {
-    const SortPlan pl = plan_for(v);
+    const SortPlan pl = plan_for(v, cap);
     SortWs w = carve(v, cap, ws, nullptr);
     const int64_t nb = n_blocks(v);
     hipError_t e = hipSuccess;
@@ -1006,8 +1191,8 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     // 1. compact surviving records in (view, id) order, keyed by depth; slot offsets in the same order
     // (the count clears the tile ranges on its way and, with few records, the record sort's
     // words, with groups of its own when there is more to clear than the records' groups would)
-    const bool few = nb <= kScanShort;
-    const OsWs dws = os_carve(v->n_gv, pl.depth, w.os);
+    const bool few = nb <= kScanShort && !pl.segs;
+    const OsWs dws = os_carve(v->n_gv, pl.depth, w.os, w.rec_seg, pl.segs);
     const SortClear dclear = few ? sort_clear(dws, pl.depth) : SortClear{};
     const int64_t clear_groups = imin(ceil_div(2 * v->n_tiles + dclear.status_words, 4 * kBlk), 256);
     k_valid_count<<<(unsigned)imax(nb, clear_groups), kBlk, 0, s>>>(bins, v->n_gv, nb, w.blk_a, w.blk_b, dclear,
@@ -1021,7 +1206,9 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
         e = scan_i64(w.blk_b, w.blk_b_off, nullptr, 0, nb, w.misc + 4, w.scan_tmp, s);
     }
     if (e != hipSuccess) return e;
-    k_compact<<<(unsigned)nb, kBlk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first);
+    k_compact<<<(unsigned)nb, kBlk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first,
+                                            pl.segs ? w.rec_seg : nullptr, w.inst_seg, v->n_gauss);
+    if (pl.segs) k_seg_tiles<<<1, kMaxSegs, 0, s>>>(v->d_views, pl.segs, w.misc, kSortTile, w.rec_seg, w.inst_seg);
     // 2. stable LSD sort of the records by depth
     // (when the last digit is one value for every key, that pass moves nothing: the
     // records stay in the buffer the pass before wrote, and its flag says so)
@@ -1051,7 +1238,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     int32_t* tvb = even ? w.tv_alt : values;
     // (and clear the tile sort's words when few: its workspace overlaps the record sort's, whose
     // error and flag the count has taken)
-    const OsWs tws = os_carve(cap, pl.tile, w.os);
+    const OsWs tws = os_carve(cap, pl.tile, w.os, w.inst_seg, pl.segs);
     k_emit<<<(unsigned)nb, kBlk, 0, s>>>(w.stiles, rva, rvb, v->n_gauss, v->d_views, w.blk_a_off, w.misc, ta, tva,
                                          few ? sort_clear(tws, pl.tile) : SortClear{}, pl.tile.passes,
                                          1 << pl.tile.digit, tws.tile);
