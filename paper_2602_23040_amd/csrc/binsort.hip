@@ -195,20 +195,6 @@ __device__ __forceinline__ int32_t block_incl_1024(int32_t v, int32_t* s_warp) {
     return v + before;
 }
 
-__device__ __forceinline__ int64_t block_incl_1024_i64(int64_t v, int64_t* s_warp) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int64_t u = __shfl_up(v, o, 64);
-        if (lane >= o) v += u;
-    }
-    if (lane == 63) s_warp[wid] = v;
-    __syncthreads();
-    int64_t before = 0;
-    for (int k = 0; k < wid; k++) before += s_warp[k];
-    return v + before;
-}
-
 __device__ __forceinline__ int64_t block_sum_1024(int64_t c, int64_t* s) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
@@ -230,60 +216,112 @@ struct SortClear {
     __device__ __forceinline__ void run(int64_t words, int64_t i0, int64_t stride) const {
         for (int64_t i = i0; i < words; i += stride) status[i] = 0ull;
         for (int64_t i = i0; i < hist_words; i += stride) hist[i] = 0u;
-            if (i0 < 2 && err) err[i0] = 0;
+        if (i0 < 2 && err) err[i0] = 0;
     }
 };
 
-__global__ __launch_bounds__(kBlk) void k_valid_count(const pg_bin* __restrict__ bins, int64_t n_gv, int64_t n_blk,
-                                                      int64_t* __restrict__ blk_cnt, int64_t* __restrict__ blk_nt,
-                                                      SortClear clear, uint32_t* __restrict__ ranges,
-                                                      int64_t range_words) {
-    __shared__ int64_t s[kBlk / 64];
-    const int64_t i0 = (int64_t)blockIdx.x * kBlk + threadIdx.x, stride = (int64_t)gridDim.x * kBlk;
+// The kernels that walk the records (k_valid_count, k_compact) take a
+// group's kBlk records with four per lane, 64 apart, so that four loads are in flight in
+// each; with one, in groups of 1,024 threads, they waited on it and on the barriers of
+// sixteen waves (k_valid_count and k_compact, us: 14.6 M records 88 and 100 -> 78 and
+// 68, 31 M records 177 and 215 -> 125 and 144).
+constexpr int kWalk = 256;
+constexpr int kWalkItems = kBlk / kWalk;
+
+__global__ __launch_bounds__(kWalk) void k_valid_count(const pg_bin* __restrict__ bins, int64_t n_gv, int64_t n_blk,
+                                                       int64_t* __restrict__ blk_cnt, int64_t* __restrict__ blk_nt,
+                                                       SortClear clear, uint32_t* __restrict__ ranges,
+                                                       int64_t range_words) {
+    __shared__ int64_t s[2][kWalk / 64];
+    const int64_t i0 = (int64_t)blockIdx.x * kWalk + threadIdx.x, stride = (int64_t)gridDim.x * kWalk;
     clear.run(clear.status_words, i0, stride);
     for (int64_t i = i0; i < range_words; i += stride) ranges[i] = 0u;
     if (blockIdx.x >= n_blk) return;      // groups that only clear
-    const int64_t gv = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    const int64_t nt = gv < n_gv ? (int64_t)bins[gv].n_tiles : 0;
-    const int64_t c = block_sum_1024(nt > 0 ? 1 : 0, s);
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t gv = (int64_t)blockIdx.x * kBlk + wid * (kBlk / 4) + lane;
+    int32_t nt[kWalkItems];
+#pragma unroll
+    for (int j = 0; j < kWalkItems; j++) nt[j] = gv + j * 64 < n_gv ? bins[gv + j * 64].n_tiles : 0;
+    int32_t c = 0;
+    int64_t t = 0;
+#pragma unroll
+    for (int j = 0; j < kWalkItems; j++) {
+        c += (int32_t)__popcll(__ballot(nt[j] > 0));
+        t += nt[j];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if (lane == 0) {
+        s[0][wid] = c;
+        s[1][wid] = t;
+    }
     __syncthreads();
-    const int64_t t = block_sum_1024(nt, s);
     if (threadIdx.x == 0) {
-        blk_cnt[blockIdx.x] = c;
-        blk_nt[blockIdx.x] = t;
+        blk_cnt[blockIdx.x] = s[0][0] + s[0][1] + s[0][2] + s[0][3];
+        blk_nt[blockIdx.x] = s[1][0] + s[1][1] + s[1][2] + s[1][3];
     }
 }
 
 // Compaction of the surviving records (key: depth bits, value: gv) and the
 // instance-slot offsets in (view, id) order: inst_first[gv] = number of
 // instances of all records before gv.
-__global__ __launch_bounds__(kBlk) void k_compact(const pg_bin* __restrict__ bins, int64_t n_gv,
-                                                  const int64_t* __restrict__ blk_off,
-                                                  const int64_t* __restrict__ blk_nt_off, uint32_t* __restrict__ rk,
-                                                  int32_t* __restrict__ rv, int32_t* __restrict__ inst_first,
-                                                  SortSeg* __restrict__ rec_seg, SortSeg* __restrict__ inst_seg,
-                                                  int64_t N) {
-    __shared__ int32_t s_warp[kBlk / 64];
-    __shared__ int64_t s_warp64[kBlk / 64];
-    const int64_t gv = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-    uint4 b = make_uint4(0u, 0u, 0u, 0u);
-    if (gv < n_gv) b = reinterpret_cast<const uint4*>(bins)[gv];
-    const int32_t valid = (gv < n_gv && b.w > 0) ? 1 : 0;
-    const int32_t incl = block_incl_1024(valid, s_warp);
-    const int64_t nt = valid ? (int64_t)b.w : 0;
-    const int64_t nt_incl = block_incl_1024_i64(nt, s_warp64);
-    if (gv < n_gv) inst_first[gv] = (int32_t)(blk_nt_off[blockIdx.x] + nt_incl - nt);
-    if (rec_seg) {      // N >= kBlk: at most one view begins in this group
-        const int64_t v = ceil_div((int64_t)blockIdx.x * kBlk, N);
-        if (gv == v * N && gv < n_gv) {
-            rec_seg[v].start = (uint32_t)(blk_off[blockIdx.x] + incl - valid);
-            inst_seg[v].start = (uint32_t)(blk_nt_off[blockIdx.x] + nt_incl - nt);
-        }
+__global__ __launch_bounds__(kWalk) void k_compact(const pg_bin* __restrict__ bins, int64_t n_gv,
+                                                   const int64_t* __restrict__ blk_off,
+                                                   const int64_t* __restrict__ blk_nt_off, uint32_t* __restrict__ rk,
+                                                   int32_t* __restrict__ rv, int32_t* __restrict__ inst_first,
+                                                   SortSeg* __restrict__ rec_seg, SortSeg* __restrict__ inst_seg,
+                                                   int64_t N) {
+    __shared__ int64_t s[2][kWalk / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t gv0 = (int64_t)blockIdx.x * kBlk + wid * (kBlk / 4) + lane;
+    uint4 b[kWalkItems];
+#pragma unroll
+    for (int j = 0; j < kWalkItems; j++) {
+        b[j] = make_uint4(0u, 0u, 0u, 0u);
+        if (gv0 + j * 64 < n_gv) b[j] = reinterpret_cast<const uint4*>(bins)[gv0 + j * 64];
     }
-    if (valid) {
-        const int64_t pos = blk_off[blockIdx.x] + incl - 1;
-        rk[pos] = b.z;
-        rv[pos] = (int32_t)gv;
+    int64_t nt_excl[kWalkItems], nt_run = 0;    // instances of the wave's records before this one
+    int32_t excl[kWalkItems], run = 0;          // ... and its surviving records
+#pragma unroll
+    for (int j = 0; j < kWalkItems; j++) {
+        const uint64_t m = __ballot((int32_t)b[j].w > 0);
+        excl[j] = run + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+        run += (int32_t)__popcll(m);
+        int64_t incl = b[j].w;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += u;
+        }
+        nt_excl[j] = nt_run + incl - b[j].w;
+        nt_run += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) {
+        s[0][wid] = run;
+        s[1][wid] = nt_run;
+    }
+    __syncthreads();
+    int64_t pos0 = blk_off[blockIdx.x], inst0 = blk_nt_off[blockIdx.x];
+    for (int w = 0; w < wid; w++) {
+        pos0 += s[0][w];
+        inst0 += s[1][w];
+    }
+    // N >= kBlk: at most one view begins in this group
+    const int64_t v = rec_seg ? ceil_div((int64_t)blockIdx.x * kBlk, N) : 0;
+#pragma unroll
+    for (int j = 0; j < kWalkItems; j++) {
+        const int64_t gv = gv0 + j * 64;
+        if (gv >= n_gv) continue;
+        inst_first[gv] = (int32_t)(inst0 + nt_excl[j]);
+        if (rec_seg && gv == v * N) {
+            rec_seg[v].start = (uint32_t)(pos0 + excl[j]);
+            inst_seg[v].start = (uint32_t)(inst0 + nt_excl[j]);
+        }
+        if ((int32_t)b[j].w > 0) {
+            const int64_t pos = pos0 + excl[j];
+            rk[pos] = b[j].z;
+            rv[pos] = (int32_t)gv;
+        }
     }
 }
 
@@ -1195,7 +1233,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     const OsWs dws = os_carve(v->n_gv, pl.depth, w.os, w.rec_seg, pl.segs);
     const SortClear dclear = few ? sort_clear(dws, pl.depth) : SortClear{};
     const int64_t clear_groups = imin(ceil_div(2 * v->n_tiles + dclear.status_words, 4 * kBlk), 256);
-    k_valid_count<<<(unsigned)imax(nb, clear_groups), kBlk, 0, s>>>(bins, v->n_gv, nb, w.blk_a, w.blk_b, dclear,
+    k_valid_count<<<(unsigned)imax(nb, clear_groups), kWalk, 0, s>>>(bins, v->n_gv, nb, w.blk_a, w.blk_b, dclear,
                                                                     reinterpret_cast<uint32_t*>(ranges),
                                                                     2 * v->n_tiles);
     if (few) {
@@ -1206,7 +1244,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
         e = scan_i64(w.blk_b, w.blk_b_off, nullptr, 0, nb, w.misc + 4, w.scan_tmp, s);
     }
     if (e != hipSuccess) return e;
-    k_compact<<<(unsigned)nb, kBlk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first,
+    k_compact<<<(unsigned)nb, kWalk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first,
                                             pl.segs ? w.rec_seg : nullptr, w.inst_seg, v->n_gauss);
     if (pl.segs) k_seg_tiles<<<1, kMaxSegs, 0, s>>>(v->d_views, pl.segs, w.misc, kSortTile, w.rec_seg, w.inst_seg);
     // 2. stable LSD sort of the records by depth
