@@ -392,14 +392,19 @@ __global__ __launch_bounds__(kBlk) void k_sorted_count(const pg_tile_set* __rest
 
 __global__ void k_sort_count(SortCount post) { post.finish(post.n_inst[0]); }
 
-// Emission in sorted-record order.  The group's 1024 records own consecutive
-// output ranges (their kept-tile counts scanned over the group); each thread
-// walks its own record's kept-tile bits in increasing order (row-major over
-// the rectangle) and writes (tile, gv) at its range, so an instance costs a
-// bit scan and one small division.  The lanes of a wave write into one
-// window of the output a few hundred instances long.  Records keeping every
-// tile of a rectangle larger than 64 tiles are rare and long: their waves
-// emit them one after another, all 64 lanes on one record.
+// Emission in sorted-record order.  The group's records own consecutive output
+// ranges (their kept-tile counts scanned over the group); each lane walks its
+// own record's kept-tile bits in increasing order (row-major over the
+// rectangle), so an instance costs a bit scan and one small division.  The 64
+// records of a wave own one window of the output, of a few hundred instances:
+// the lanes write it to LDS, and the wave copies it out in whole lines (written
+// straight from the lanes, every instance was a store address of its own: 160,
+// 344 and 264 us for 38, 78 and 65 M instances, now 129, 226 and 242; two groups
+// fit a CU, and a buffer that leaves room for one is slower).  Windows longer
+// than the buffer are written directly, as are records keeping every tile of a
+// rectangle larger than 64 tiles, which are rare and long: their waves emit them
+// one after another, all 64 lanes on one record.
+constexpr int kEmitStage = 608;      // instances of a wave's window that LDS holds
 __device__ __forceinline__ void rect_tile(int32_t k, int32_t w, float rw, int32_t& row, int32_t& col) {
     // row = k / w from a float estimate (k < 2^24), corrected to the exact quotient
     row = (int32_t)((float)k * rw);
@@ -416,6 +421,7 @@ __global__ __launch_bounds__(kBlk) void k_emit(const uint4* __restrict__ stiles,
                                                SortClear clear, int32_t passes, int32_t nb, int32_t tile) {
     const int32_t* __restrict__ rv = misc[5] ? rv_stayed : rv_moved;   // as in k_sorted_count
     __shared__ int32_t s_warp[kBlk / 64];
+    __shared__ uint2 s_out[kBlk / 64][kEmitStage];
     // the tile sort's words (its workspace overlaps the record sort's, which is done): status
     // is [pass][tile][nb], of which the device-side count needs the first tiles
     if (clear.err) {
@@ -436,15 +442,38 @@ __global__ __launch_bounds__(kBlk) void k_emit(const uint4* __restrict__ stiles,
         const uint4 ts = stiles[p];
         nt = kept_count(ts);
         const int32_t xlo = (int32_t)(ts.z & 0xffff), ylo = (int32_t)(ts.z >> 16);
-        const ViewDev& V = views[gv / N];
+        const ViewDev& V = views[(uint32_t)gv / (uint32_t)N];
         w = (int32_t)(ts.w & 0xffff);
         tx = V.TX;
         tile0 = (uint32_t)(V.tile_base + (int64_t)ylo * V.TX + xlo);
         mask = (uint64_t)ts.x | ((uint64_t)ts.y << 32);
     }
     const int32_t incl = block_incl_1024(nt, s_warp);
-    const int64_t e0 = blk_off[blockIdx.x] + incl - nt;     // this record's first output
+    const int32_t o0 = incl - nt;                                      // first output in the group
+    const int32_t w0 = __builtin_amdgcn_readfirstlane(o0);             // ... of the wave's window
+    const int32_t total = __builtin_amdgcn_readlane(incl, 63) - w0;
+    const int64_t base = blk_off[blockIdx.x];
     const float rw = 1.0f / (float)w;
+    uint64_t big = __ballot(mask == 0 && nt > 0);
+    if (big == 0 && total <= kEmitStage) {
+        uint2* out = s_out[t >> 6];
+        int32_t e = o0 - w0;
+        for (uint64_t m = mask; m != 0; e++) {
+            const int32_t bit = (int32_t)__builtin_ctzll(m);
+            m &= m - 1;
+            int32_t row, col;
+            rect_tile(bit, w, rw, row, col);
+            out[e] = make_uint2(tile0 + (uint32_t)(row * tx + col), (uint32_t)gv);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the buffer is the wave's own
+        for (int32_t i = lane; i < total; i += 64) {
+            const uint2 kv = out[i];
+            tkeys[base + w0 + i] = kv.x;
+            tvals[base + w0 + i] = (int32_t)kv.y;
+        }
+        return;
+    }
+    const int64_t e0 = base + o0;
     if (mask != 0) {
         uint64_t m = mask;
         for (int64_t e = e0; m != 0; e++) {
@@ -457,7 +486,6 @@ __global__ __launch_bounds__(kBlk) void k_emit(const uint4* __restrict__ stiles,
         }
     }
     // records that keep every tile of their rectangle, one at a time per wave
-    uint64_t big = __ballot(mask == 0 && nt > 0);
     while (big) {
         const int src = __builtin_ctzll(big);
         big &= big - 1;
