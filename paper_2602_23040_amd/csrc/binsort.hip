@@ -53,7 +53,7 @@ struct DigitPlan {
     int passes, digit;      // LSD passes of equal width digit bits
 };
 constexpr int kOsMaxBits = 9;                // digit width the radix pass kernels are built for
-constexpr int kDepthDigitBits = 8;           // digit width caps of the record (depth) and instance (tile) sorts
+constexpr int kDepthDigitBits = 8, kDepthPasses = 4;   // digit width caps of the record (depth) and instance (tile) sorts
 constexpr int kTileDigitBits = 7;            // 18-bit tile ids: 3 x 6 bits; 19-21 bits: 3 x 7 instead of 4 x 5
 
 DigitPlan digit_plan(int bits, int max_bits) {
@@ -262,67 +262,141 @@ __global__ __launch_bounds__(kWalk) void k_valid_count(const pg_bin* __restrict_
     }
 }
 
+// One key's digits into a wave's LDS histogram sw[p NB + d].  A wave whose active
+// lanes share a digit adds once (depth keys share their high bits, which would
+// otherwise serialise the LDS atomics).
+template <int BITS>
+__device__ __forceinline__ void count_key(uint32_t key, bool active, int passes, uint32_t* __restrict__ sw) {
+    constexpr int NB = 1 << BITS;
+    const uint64_t act = __ballot(active);
+    if (act == 0) return;
+    const int lane = threadIdx.x & 63, lead = __builtin_ctzll(act);
+    for (int p = 0; p < passes; p++) {
+        const uint32_t d = (key >> (p * BITS)) & (NB - 1);
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, lead);
+        if (__ballot(active && d == d0) == act) {
+            if (lane == lead) atomicAdd(&sw[p * NB + d0], (uint32_t)__popcll(act));   // counts only: order-free
+        } else if (active) {
+            atomicAdd(&sw[p * NB + d], 1u);
+        }
+    }
+}
+
 // Compaction of the surviving records (key: depth bits, value: gv) and the
 // instance-slot offsets in (view, id) order: inst_first[gv] = number of
-// instances of all records before gv.
+// instances of all records before gv.  HIST (views sorted apart): a group takes
+// `run` consecutive groups of records, counts their depth digits into
+// hist[view][pass][digit] on the way, and notes where the views begin.  The
+// counts are bound by LDS atomics and the compaction by memory, so counting here
+// costs less than a pass over the keys (us, compaction and counting pass / both here:
+// 14.6 M records 68 + 68 / 104, 31 M 144 + 135 / 220).
+template <bool HIST>
 __global__ __launch_bounds__(kWalk) void k_compact(const pg_bin* __restrict__ bins, int64_t n_gv,
                                                    const int64_t* __restrict__ blk_off,
                                                    const int64_t* __restrict__ blk_nt_off, uint32_t* __restrict__ rk,
                                                    int32_t* __restrict__ rv, int32_t* __restrict__ inst_first,
-                                                   SortSeg* __restrict__ rec_seg, SortSeg* __restrict__ inst_seg,
-                                                   int64_t N) {
+                                                   int64_t n_blk, int32_t run, SortSeg* __restrict__ rec_seg,
+                                                   SortSeg* __restrict__ inst_seg, int64_t N,
+                                                   uint32_t* __restrict__ hist) {
+    constexpr int kWords = kDepthPasses << kDepthDigitBits;
     __shared__ int64_t s[2][kWalk / 64];
+    __shared__ uint32_t s_hist[HIST ? kWalk / 64 : 1][HIST ? kWords : 1];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int64_t gv0 = (int64_t)blockIdx.x * kBlk + wid * (kBlk / 4) + lane;
-    uint4 b[kWalkItems];
+    const int64_t g0 = HIST ? (int64_t)blockIdx.x * run : blockIdx.x, g1 = HIST ? imin(g0 + run, n_blk) : g0 + 1;
+    int64_t v = 0;              // HIST: the view being counted
+    auto flush = [&]() {        // its counts, and a clean histogram for the next
+        __syncthreads();
+        for (int i = threadIdx.x; i < kWords; i += kWalk) {
+            uint32_t c = 0;
 #pragma unroll
-    for (int j = 0; j < kWalkItems; j++) {
-        b[j] = make_uint4(0u, 0u, 0u, 0u);
-        if (gv0 + j * 64 < n_gv) b[j] = reinterpret_cast<const uint4*>(bins)[gv0 + j * 64];
-    }
-    int64_t nt_excl[kWalkItems], nt_run = 0;    // instances of the wave's records before this one
-    int32_t excl[kWalkItems], run = 0;          // ... and its surviving records
-#pragma unroll
-    for (int j = 0; j < kWalkItems; j++) {
-        const uint64_t m = __ballot((int32_t)b[j].w > 0);
-        excl[j] = run + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
-        run += (int32_t)__popcll(m);
-        int64_t incl = b[j].w;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int64_t u = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += u;
+            for (int w = 0; w < kWalk / 64; w++) {
+                c += s_hist[w][i];
+                s_hist[w][i] = 0u;
+            }
+            if (c) atomicAdd(&hist[v * kWords + i], c);
         }
-        nt_excl[j] = nt_run + incl - b[j].w;
-        nt_run += __shfl(incl, 63, 64);
-    }
-    if (lane == 0) {
-        s[0][wid] = run;
-        s[1][wid] = nt_run;
-    }
-    __syncthreads();
-    int64_t pos0 = blk_off[blockIdx.x], inst0 = blk_nt_off[blockIdx.x];
-    for (int w = 0; w < wid; w++) {
-        pos0 += s[0][w];
-        inst0 += s[1][w];
-    }
-    // N >= kBlk: at most one view begins in this group
-    const int64_t v = rec_seg ? ceil_div((int64_t)blockIdx.x * kBlk, N) : 0;
+        __syncthreads();
+    };
+    if (HIST) {
+        v = g0 > 0 ? (g0 * kBlk - 1) / N : 0;       // the view of the record before this run
+        for (int i = threadIdx.x; i < kWords; i += kWalk) {
 #pragma unroll
-    for (int j = 0; j < kWalkItems; j++) {
-        const int64_t gv = gv0 + j * 64;
-        if (gv >= n_gv) continue;
-        inst_first[gv] = (int32_t)(inst0 + nt_excl[j]);
-        if (rec_seg && gv == v * N) {
-            rec_seg[v].start = (uint32_t)(pos0 + excl[j]);
-            inst_seg[v].start = (uint32_t)(inst0 + nt_excl[j]);
+            for (int w = 0; w < kWalk / 64; w++) s_hist[w][i] = 0u;
         }
-        if ((int32_t)b[j].w > 0) {
-            const int64_t pos = pos0 + excl[j];
-            rk[pos] = b[j].z;
-            rv[pos] = (int32_t)gv;
+        __syncthreads();
+    }
+    for (int64_t g = g0; g < g1; g++) {
+        const int64_t gv0 = g * kBlk + wid * (kBlk / 4) + lane;
+        uint4 b[kWalkItems];
+#pragma unroll
+        for (int j = 0; j < kWalkItems; j++) {
+            b[j] = make_uint4(0u, 0u, 0u, 0u);
+            if (gv0 + j * 64 < n_gv) b[j] = reinterpret_cast<const uint4*>(bins)[gv0 + j * 64];
+        }
+        int64_t nt_excl[kWalkItems], nt_run = 0;    // instances of the wave's records before this one
+        int32_t excl[kWalkItems], kept = 0;         // ... and its surviving records
+#pragma unroll
+        for (int j = 0; j < kWalkItems; j++) {
+            const uint64_t m = __ballot((int32_t)b[j].w > 0);
+            excl[j] = kept + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+            kept += (int32_t)__popcll(m);
+            int64_t incl = b[j].w;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int64_t u = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += u;
+            }
+            nt_excl[j] = nt_run + incl - b[j].w;
+            nt_run += __shfl(incl, 63, 64);
+        }
+        if (HIST) __syncthreads();      // the group before has read s
+        if (lane == 0) {
+            s[0][wid] = kept;
+            s[1][wid] = nt_run;
+        }
+        __syncthreads();
+        int64_t pos0 = blk_off[g], inst0 = blk_nt_off[g];
+        for (int w = 0; w < wid; w++) {
+            pos0 += s[0][w];
+            inst0 += s[1][w];
+        }
+#pragma unroll
+        for (int j = 0; j < kWalkItems; j++) {
+            const int64_t gv = gv0 + j * 64;
+            if (gv >= n_gv) continue;
+            inst_first[gv] = (int32_t)(inst0 + nt_excl[j]);
+            if ((int32_t)b[j].w > 0) {
+                const int64_t pos = pos0 + excl[j];
+                rk[pos] = b[j].z;
+                rv[pos] = (int32_t)gv;
+            }
+        }
+        if (!HIST) continue;
+        // N >= kBlk: at most one view begins in these records (the first one's at gv 0)
+        const int64_t first = g == 0 ? 0 : (v + 1) * N, vn = g == 0 ? 0 : v + 1;
+        const bool begins = first < imin((g + 1) * kBlk, n_gv);
+#pragma unroll
+        for (int j = 0; j < kWalkItems; j++) {
+            if (begins && gv0 + j * 64 == first) {
+                rec_seg[vn].start = (uint32_t)(pos0 + excl[j]);
+                inst_seg[vn].start = (uint32_t)(inst0 + nt_excl[j]);
+            }
+        }
+        const int64_t end = begins && vn > v ? first : (g + 1) * kBlk;      // of view v's records here
+#pragma unroll
+        for (int j = 0; j < kWalkItems; j++)
+            count_key<kDepthDigitBits>(b[j].z, (int32_t)b[j].w > 0 && gv0 + j * 64 < end, kDepthPasses,
+                                             s_hist[wid]);
+        if (begins && vn > v) {
+            flush();
+            v = vn;
+#pragma unroll
+            for (int j = 0; j < kWalkItems; j++)
+                count_key<kDepthDigitBits>(b[j].z, (int32_t)b[j].w > 0 && gv0 + j * 64 >= end, kDepthPasses,
+                                                 s_hist[wid]);
         }
     }
+    if (HIST) flush();
 }
 
 // The views' runs of records and instances from their starts (k_compact).
@@ -653,7 +727,6 @@ template <int BITS, bool UNIFORM, int KPT>
 __device__ __forceinline__ void os_count(const uint32_t* __restrict__ keys, int64_t base, int64_t n, uint32_t key0,
                                          int passes, uint32_t* __restrict__ sw) {
     constexpr int NB = 1 << BITS;
-    const int lane = threadIdx.x & 63;
     uint32_t k[KPT];
 #pragma unroll
     for (int j = 0; j < KPT; j++) {
@@ -663,22 +736,10 @@ __device__ __forceinline__ void os_count(const uint32_t* __restrict__ keys, int6
 #pragma unroll
     for (int j = 0; j < KPT; j++) {
         const bool active = base + (int64_t)j * 256 + threadIdx.x < n;
-        if (!UNIFORM) {
-            if (active)
-                for (int p = 0; p < passes; p++) atomicAdd(&sw[p * NB + ((k[j] >> (p * BITS)) & (NB - 1))], 1u);
-            continue;
-        }
-        const uint64_t act = __ballot(active);
-        if (act == 0) break;
-        const int lead = __builtin_ctzll(act);
-        for (int p = 0; p < passes; p++) {
-            const uint32_t d = (k[j] >> (p * BITS)) & (NB - 1);
-            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, lead);
-            if (__ballot(active && d == d0) == act) {
-                if (lane == lead) atomicAdd(&sw[p * NB + d0], (uint32_t)__popcll(act));   // counts only: order-free
-            } else if (active) {
-                atomicAdd(&sw[p * NB + d], 1u);
-            }
+        if (UNIFORM) {
+            count_key<BITS>(k[j], active, passes, sw);
+        } else if (active) {
+            for (int p = 0; p < passes; p++) atomicAdd(&sw[p * NB + ((k[j] >> (p * BITS)) & (NB - 1))], 1u);
         }
     }
 }
@@ -717,7 +778,7 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
 
 // The digit counts of views sorted apart, hist[(v passes + p) NB + d]: a group takes a
 // run of consecutive radix tiles and adds its counts whenever the view changes.
-template <int BITS, bool UNIFORM, int KPT>
+template <int BITS, int KPT>
 __global__ __launch_bounds__(256) void k_os_hist_seg(const uint32_t* __restrict__ keys,
                                                      const int64_t* __restrict__ n_ptr,
                                                      const SortSeg* __restrict__ segs, int32_t n_segs, int passes,
@@ -742,8 +803,8 @@ __global__ __launch_bounds__(256) void k_os_hist_seg(const uint32_t* __restrict_
         if (cur < 0) return;      // never with a whole table: every tile below `tiles` has its run
         const uint32_t e = min(b1, seg.tile_first + (seg.len + kTile - 1) / kTile);
         for (; b < e; b++)
-            os_count<BITS, UNIFORM, KPT>(keys, seg.start + (int64_t)(b - seg.tile_first) * kTile,
-                                         (int64_t)seg.start + seg.len, seg.base, passes, s[threadIdx.x >> 6]);
+            os_count<BITS, false, KPT>(keys, seg.start + (int64_t)(b - seg.tile_first) * kTile,
+                                       (int64_t)seg.start + seg.len, seg.base, passes, s[threadIdx.x >> 6]);
         __syncthreads();
         for (int i = threadIdx.x; i < passes * NB; i += 256) {
             const uint32_t c = s[0][i] + s[1][i] + s[2][i] + s[3][i];
@@ -973,32 +1034,37 @@ SortClear sort_clear(const OsWs& w, DigitPlan pl) {
     return {w.status, (int64_t)pl.passes * w.tiles_max * nb, w.hist, pl.passes * nb, w.err};
 }
 
+void os_clear(DigitPlan pl, const int64_t* n_ptr, const OsWs& w, hipStream_t s) {
+    k_os_clear<<<1024, 256, 0, s>>>(n_ptr, w.tile, pl.passes, 1 << pl.digit, w.tiles_max, w.status, w.hist, w.uni,
+                                    w.n_segs, w.err);
+}
+
 // Stable LSD sort of the *n_ptr (<= cap) pairs in (ka, va) by their low
 // pl.passes * pl.digit key bits, ping-ponging with (kb, vb); the result
 // lands in (ka, va) for an even number of passes, else in (kb, vb).
 // uniform_high: keys whose high digits mostly agree (depth bits), counted with
 // the wave-uniform shortcut.  last_may_stay: when the last pass's digit is one
 // value for every key, that pass moves nothing and the result stays where the
-// pass before left it; w.uni[passes - 1] tells the caller which.
+// pass before left it; w.uni[passes - 1] tells the caller which.  few: the words are
+// cleared and the histogram is scanned by kernels around it; counted: they are cleared
+// and the digits are counted.
 hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, int32_t* vb, const int64_t* n_ptr,
-                         int64_t cap, OsWs w, bool uniform_high, bool last_may_stay, bool few, hipStream_t s) {
+                         int64_t cap, OsWs w, bool uniform_high, bool last_may_stay, bool few, bool counted,
+                         hipStream_t s) {
     const int nb = 1 << pl.digit;
     int32_t* finished = few ? w.err + 1 : nullptr;
-    if (!few)
-        k_os_clear<<<1024, 256, 0, s>>>(n_ptr, w.tile, pl.passes, nb, w.tiles_max, w.status, w.hist, w.uni, w.n_segs,
-                                        w.err);
+    if (!few && !counted) os_clear(pl, n_ptr, w, s);
     const bool small = w.tile == kSortThreads * kSmallItems;
     const unsigned hgrid = (unsigned)imax(1, imin(2048, ceil_div(imax(cap, 1), w.tile)));
-    switch (pl.digit) {
+    if (!counted) switch (pl.digit) {
 #define PG_HIST_AS(B, U, K) \
     k_os_hist<B, U, K><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished)
-#define PG_HIST_SEG(B, U) \
-    k_os_hist_seg<B, U, kSortItems><<<hgrid, 256, 0, s>>>(ka, n_ptr, w.segs, w.n_segs, pl.passes, w.hist)
+#define PG_HIST_SEG(B) \
+    k_os_hist_seg<B, kSortItems><<<hgrid, 256, 0, s>>>(ka, n_ptr, w.segs, w.n_segs, pl.passes, w.hist)
 #define PG_HIST(B)                                                  \
     case B:                                                         \
         if (w.n_segs) {                                             \
-            if (uniform_high) PG_HIST_SEG(B, true);                 \
-            else PG_HIST_SEG(B, false);                             \
+            PG_HIST_SEG(B);                                         \
         } else if (uniform_high) {                                  \
             if (small) PG_HIST_AS(B, true, kSmallItems);            \
             else PG_HIST_AS(B, true, kSortItems);                   \
@@ -1224,7 +1290,7 @@ hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t
                       int64_t cap, int bits, void* ws, uint32_t** out_keys, int32_t** out_vals, hipStream_t s) {
     const DigitPlan pl = digit_plan(bits, kDepthDigitBits);
     const OsWs w = os_carve(cap, pl, (char*)ws);
-    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, w, true, false, false, s);
+    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, w, true, false, false, false, s);
     const bool even = pl.passes % 2 == 0;
     *out_keys = even ? keys : keys_alt;
     *out_vals = even ? vals : vals_alt;
@@ -1259,14 +1325,14 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     // 1. compact surviving records in (view, id) order, keyed by depth; slot offsets in the same order
     // (the count clears the tile ranges on its way and, with few records, the record sort's
     // words, with groups of its own when there is more to clear than the records' groups would)
-    const bool few = nb <= kScanShort && !pl.segs;
+    const bool short_scan = nb <= kScanShort, few = short_scan && !pl.segs;
     const OsWs dws = os_carve(v->n_gv, pl.depth, w.os, w.rec_seg, pl.segs);
     const SortClear dclear = few ? sort_clear(dws, pl.depth) : SortClear{};
     const int64_t clear_groups = imin(ceil_div(2 * v->n_tiles + dclear.status_words, 4 * kBlk), 256);
     k_valid_count<<<(unsigned)imax(nb, clear_groups), kWalk, 0, s>>>(bins, v->n_gv, nb, w.blk_a, w.blk_b, dclear,
                                                                     reinterpret_cast<uint32_t*>(ranges),
                                                                     2 * v->n_tiles);
-    if (few) {
+    if (short_scan) {
         e = scan_short_i64({w.blk_a, w.blk_a_off, w.misc + 0}, {w.blk_b, w.blk_b_off, w.misc + 4}, nb, {}, s);
     } else {
         e = scan_i64(w.blk_a, w.blk_a_off, nullptr, 0, nb, w.misc + 0, w.scan_tmp, s);
@@ -1274,13 +1340,21 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
         e = scan_i64(w.blk_b, w.blk_b_off, nullptr, 0, nb, w.misc + 4, w.scan_tmp, s);
     }
     if (e != hipSuccess) return e;
-    k_compact<<<(unsigned)nb, kWalk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first,
-                                            pl.segs ? w.rec_seg : nullptr, w.inst_seg, v->n_gauss);
-    if (pl.segs) k_seg_tiles<<<1, kMaxSegs, 0, s>>>(v->d_views, pl.segs, w.misc, kSortTile, w.rec_seg, w.inst_seg);
+    if (pl.segs) {
+        os_clear(pl.depth, w.misc + 0, dws, s);
+        const int32_t run = (int32_t)imax(2, ceil_div(nb, 2048));    // groups of records per work-group
+        k_compact<true><<<(unsigned)ceil_div(nb, run), kWalk, 0, s>>>(
+            bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0, inst_first, nb, run, w.rec_seg, w.inst_seg,
+            v->n_gauss, dws.hist);
+        k_seg_tiles<<<1, kMaxSegs, 0, s>>>(v->d_views, pl.segs, w.misc, kSortTile, w.rec_seg, w.inst_seg);
+    } else {
+        k_compact<false><<<(unsigned)nb, kWalk, 0, s>>>(bins, v->n_gv, w.blk_a_off, w.blk_b_off, w.rk0, w.rv0,
+                                                        inst_first, nb, 1, nullptr, nullptr, v->n_gauss, nullptr);
+    }
     // 2. stable LSD sort of the records by depth
     // (when the last digit is one value for every key, that pass moves nothing: the
     // records stay in the buffer the pass before wrote, and its flag says so)
-    e = onesweep_sort(pl.depth, w.rk0, w.rv0, w.rk1, w.rv1, w.misc + 0, v->n_gv, dws, true, true, few, s);
+    e = onesweep_sort(pl.depth, w.rk0, w.rv0, w.rk1, w.rv1, w.misc + 0, v->n_gv, dws, true, true, few, pl.segs != 0, s);
     if (e != hipSuccess) return e;
     const int32_t* rva = pl.depth.passes % 2 == 0 ? w.rv0 : w.rv1;
     const int32_t* rvb = pl.depth.passes % 2 == 0 ? w.rv1 : w.rv0;
@@ -1290,7 +1364,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
     SortCount count = post;
     count.err = dws.err;
     count.stayed = stayed;
-    if (few) {
+    if (short_scan) {
         e = scan_short_i64({w.blk_a, w.blk_a_off, nullptr}, {}, nb, count, s);
         if (e != hipSuccess) return e;
     } else {
@@ -1311,7 +1385,7 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
                                          few ? sort_clear(tws, pl.tile) : SortClear{}, pl.tile.passes,
                                          1 << pl.tile.digit, tws.tile);
     // 5. stable LSD sort of the instances by tile id
-    e = onesweep_sort(pl.tile, ta, tva, tb, tvb, w.misc + 1, cap, tws, false, false, few, s);
+    e = onesweep_sort(pl.tile, ta, tva, tb, tvb, w.misc + 1, cap, tws, false, false, few, false, s);
     if (e != hipSuccess) return e;
     k_ranges<<<(unsigned)imax(1, imin(kRangeGrid, ceil_div(cap, 256))), 256, 0, s>>>(keys, w.misc, ranges, tws.err,
                                                                                      overflow_dev);
