@@ -75,8 +75,8 @@ struct SortPlan {
 };
 
 constexpr int kMaxSegs = 1024;                   // views sorted apart: a thread of k_seg_tiles each
-constexpr int64_t kSegRecords = 1 << 19;         // records from which views are sorted apart: to save a pass
-constexpr int64_t kSegRecordsAny = 1 << 21;      // ... and with no pass to save
+constexpr int64_t kSegRecords = 1 << 18;         // records from which views are sorted apart
+constexpr int64_t kSegRecordsPass = 1 << 17;     // ... where it saves a tile pass
 
 int view_bits(const pg_views* v) {
     int64_t most = 1;
@@ -87,22 +87,25 @@ int view_bits(const pg_views* v) {
 }
 
 // Views sorted apart: the tile ids inside one view need fewer bits than those of all
-// views (two passes of 6 bits instead of three at 50 views of 1024 x 768), and records in
-// (view, depth) order gather their tile sets from one view's array at a time.  It costs
-// the launches that small sorts fold into other kernels, and a partly filled radix tile
-// per view.  pg_bin_sort, one sort / views apart, us: 50 views x 293 k records (38 M
-// instances) 1731 / 1370, 8 x 4 frames of 1080p (78 M) 2972 / 2490, 10 x 3.1 M (65 M)
-// 3274 / 3046; 16 x 262 k 569 / 448, 12 x 65 k 219 / 198, 8 x 65 k 189 / 183, 5 x 65 k
-// 186 / 186, 3 x 65 k 156 / 170; with the passes alike, 3 x 1 M 448 / 425, 2 x 1 M
-// 420 / 425, 4 x 262 k 214 / 218, 2 x 524 k 267 / 280.
+// views (two passes of 6 bits instead of three at 50 views of 1024 x 768), the records
+// in (view, depth) order gather their tile sets from one view's array at a time, and
+// their digits are counted in the compaction.  It costs the launches that small sorts
+// fold into other kernels, and a partly filled radix tile per view.  pg_bin_sort, one
+// sort / views apart, us: 2 x 1 M records 388 / 367, 16 x 65 k 201 / 166, 4 x 65 k
+// 166 / 140, 200 x 1.6 k 167 / 128; 3 x 65 k 153 / 137 and 3 x 32 k 129 / 125 with a pass
+// saved, 3 x 65 k 122 / 124, 8 x 16 k 117 / 121 and 2 x 16 k 129 / 147 without; one view
+// of 293 k 154 / 164, of 4.2 M 499 / 499.  The large ones with the digits still counted in
+// a pass of their own: 50 views x 293 k (38 M instances) 1731 / 1370, 8 x 4 frames of
+// 1080p (78 M) 2972 / 2490, 10 x 3.1 M (65 M) 3274 / 3046.
 SortPlan plan_for(const pg_views* v, int64_t cap) {
     SortPlan p;
     p.segs = 0;
     p.depth = digit_plan(32, kDepthDigitBits);
     p.tile = digit_plan(v->key_bits, kTileDigitBits);   // ceil(log2(n_tiles)), >= 1
-    if (v->n_gv >= kSegRecords && cap > kSmallSort && v->n_gauss >= kBlk && v->n_views <= kMaxSegs) {
+    if (v->n_gv >= kSegRecordsPass && cap > kSmallSort && v->n_gauss >= kBlk && v->n_views > 1 &&
+        v->n_views <= kMaxSegs) {
         const DigitPlan apart = digit_plan(view_bits(v), kTileDigitBits);   // ... of the largest view
-        if (apart.passes < p.tile.passes || (v->n_gv >= kSegRecordsAny && v->n_views > 2)) {
+        if (apart.passes < p.tile.passes || v->n_gv >= kSegRecords) {
             p.segs = v->n_views;
             p.tile = apart;
         }

@@ -1,6 +1,6 @@
 """pg_bin_sort with its views sorted apart, against a numpy sort of the projection's
 bins and tile sets over all views: record counts on both sides of the limits of
-that path (2^19 records where it saves a pass, 2^21 otherwise), runs that end on
+that path (2^18 records, 2^17 where it saves a pass), runs that end on
 and off the 1,024 records of a compaction group and the 4,096 pairs of a radix
 work-group, views of two sizes, views that see nothing at either end, and depths
 whose high digit is one value in all views, in some, or in none.  Every output is
@@ -16,7 +16,11 @@ from test_gpu_sort_paths import expected
 pytestmark = pytest.mark.gpu
 
 # records per view, views, sizes, camera distance, views that see nothing, views moved back
-CASES = [(9000, 60, ((160, 120), (64, 48)), 4.0, (0, 7, 59), ()),
+CASES = [(2048, 64, ((160, 120),), 8.0, (), (3,)),
+         (2047, 64, ((160, 120),), 8.0, (), (3,)),
+         (4096, 64, ((320, 240),), 8.0, (63,), (3,)),
+         (4095, 64, ((320, 240),), 8.0, (63,), (3,)),
+         (9000, 60, ((160, 120), (64, 48)), 4.0, (0, 7, 59), ()),
          (8192, 70, ((160, 120),), 8.0, (), (3, 4)),
          (8191, 64, ((160, 120),), 8.0, (), (3,)),
          (1024, 600, ((64, 48),), 20.0, (599,), (0,)),
