@@ -490,8 +490,10 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 //  1. An FP32 bound per record: a disc around the mean that contains the exact
 //     square (the largest scale through the Jacobian's norm, every rounding
 //     covered), and whether a motion cell lies under it.  Most records end
-//     here after ~80 instructions instead of the FP64 projection's ~450, and a
-//     Gaussian that an earlier view has already labelled ends at once.
+//     here after ~80 instructions instead of the FP64 projection's ~450.  A
+//     Gaussian that an earlier view has already labelled ends at once; where the
+//     groups are many rounds of the chip, most are, and the others are first
+//     collected in LDS so that every lane has one.
 //  2. The records left are collected in LDS, so that every lane has one: the
 //     FP64 projection, culls and radius of k_project, and the cells under the
 //     ellipse's box.  Then eight lanes take a record and scan the box's rows
@@ -505,8 +507,9 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 // XCD for every view, so its parameters and labels stay in that L2.
 // 14.0 M records of 50 views of 1024x768, 3 % of motion: the whole call 1,720 us
 // with the FP64 projection of every record and a wave per flagged record; 575
-// with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles
-// (of which the fetch, the cells and the first phase are 260).
+// with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles;
+// 339 with the unlabelled records collected and the next one's parameters read
+// ahead.
 constexpr int kFlowThreads = 256;
 constexpr int kFlowRecs = 2048;        // Gaussians per work-group at most
 constexpr int64_t kFlowFill = 2048;    // work-groups that fill the chip
@@ -579,11 +582,14 @@ __global__ void k_fill_u8(uint8_t* __restrict__ p, int64_t n) {
 // False when the record is certainly static in this view: culled by depth, or
 // no motion cell under a square that contains the exact one.
 // e = 2^-21 bounds eight FP32 roundings; each quantity carries its own bound.
-__device__ __forceinline__ bool flow_may_hit(const ViewDev& V, float rn2, const float* __restrict__ P, int64_t N,
-                                             int32_t tw, int32_t th, const uint8_t* __restrict__ tmot) {
+struct Shape {
+    float x, y, z, s0, s1, s2;      // position, log scales
+};
+__device__ __forceinline__ bool flow_may_hit(const ViewDev& V, float rn2, const Shape& g, int32_t tw, int32_t th,
+                                             const uint8_t* __restrict__ tmot) {
     constexpr float e = 4.76837158e-7f;
-    const float x = P[0], y = P[N], z = P[2 * N];
-    const float ls = fmaxf(fmaxf(P[3 * N], P[4 * N]), P[5 * N]);
+    const float x = g.x, y = g.y, z = g.z;
+    const float ls = fmaxf(fmaxf(g.s0, g.s1), g.s2);
     const float* R = V.Rf;
     const float xc = fmaf(R[0], x, fmaf(R[1], y, fmaf(R[2], z, V.tf[0])));
     const float yc = fmaf(R[3], x, fmaf(R[4], y, fmaf(R[5], z, V.tf[1])));
@@ -624,15 +630,15 @@ struct Square {
 };
 
 __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __restrict__ views, int32_t nv, int32_t C,
-                                                            int64_t N, int32_t recs, int64_t n_pixels, int32_t tw,
-                                                            int32_t th,
+                                                            int64_t N, int32_t recs, int32_t open, int64_t n_pixels,
+                                                            int32_t tw, int32_t th,
                                                             const float* __restrict__ params,
                                                             const uint8_t* __restrict__ masks,
                                                             const uint8_t* __restrict__ tmot, uint8_t* dyn_gauss,
                                                             unsigned long long* __restrict__ counters) {
-    __shared__ uint16_t s_rec[kFlowRecs];
+    __shared__ uint16_t s_open[kFlowRecs], s_rec[kFlowRecs];
     __shared__ Square s_sq[kFlowThreads];
-    __shared__ int32_t s_count;
+    __shared__ int32_t s_left, s_count;
     // work-group b runs on XCD b mod 8: chunks of Gaussians are dealt to the XCDs,
     // and an XCD takes its chunks view by view
     const int64_t chunks = ceil_div(N, recs), per = ceil_div(chunks, 8);
@@ -645,7 +651,7 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
     const float* P0 = params + (int64_t)V.frame * C * N;
     const int64_t out0 = (int64_t)V.frame * N;
     uint64_t tests = 0;
-    if (threadIdx.x == 0) s_count = 0;
+    if (threadIdx.x == 0) s_left = s_count = 0;
     // |R R^T| bounds the squared norm of the camera matrix (1 for a rotation)
     float rn2 = 0.0f;
 #pragma unroll
@@ -657,20 +663,55 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
         rn2 = fmaxf(rn2, sum);
     }
     __syncthreads();
-    // ---- phase 1
-    for (int k = threadIdx.x; k < recs; k += kFlowThreads) {
-        const int64_t i = i0 + k;
-        bool keep = i < N;
-        // labelled by an earlier view (a stale 0 only costs the test; with the test
-        // counter the labels are not looked at, so the count is the same every time)
-        const bool labelled = keep && !counters &&
-            __hip_atomic_load(dyn_gauss + out0 + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
-        if (keep) keep = flow_may_hit(V, rn2, P0 + i, N, tw, th, tmot) && !labelled;
+    // appends the lanes' records to a list (in any order)
+    auto append = [&](bool keep, int32_t k, uint16_t* list, int32_t* n) __attribute__((always_inline)) {
         const uint64_t m = __ballot(keep);
         int32_t at = 0;
-        if (lane == 0 && m) at = atomicAdd(&s_count, (int32_t)__popcll(m));
+        if (lane == 0 && m) at = atomicAdd(n, (int32_t)__popcll(m));
         at = __builtin_amdgcn_readfirstlane(at);
-        if (keep) s_rec[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = (uint16_t)k;
+        if (keep) list[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = (uint16_t)k;
+    };
+    // an earlier view's label ends a record (a stale 0 only costs the test; with the test
+    // counter the labels are not looked at, so the count is the same every time)
+    auto labelled = [&](int32_t k) __attribute__((always_inline)) {
+        return !counters && __hip_atomic_load(dyn_gauss + out0 + i0 + k, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
+    };
+    int32_t left = (int32_t)imin(recs, N - i0);
+    if (open) {     // the records without a label, collected so that every lane has one
+        bool keep[kFlowRecs / kFlowThreads];
+#pragma unroll
+        for (int q = 0; q < kFlowRecs / kFlowThreads; q++) {
+            const int32_t k = (int32_t)threadIdx.x + q * kFlowThreads;
+            keep[q] = k < left && !labelled(k);
+        }
+#pragma unroll
+        for (int q = 0; q < kFlowRecs / kFlowThreads; q++)
+            append(keep[q], (int32_t)threadIdx.x + q * kFlowThreads, s_open, &s_left);
+        __syncthreads();
+        left = s_left;
+    }
+    // ---- phase 1: the next record's parameters are read while one is tested
+    auto record = [&](int32_t at) __attribute__((always_inline)) {
+        at = min(at, left - 1);
+        return open ? (int32_t)s_open[at] : at;
+    };
+    auto shape = [&](int32_t k) __attribute__((always_inline)) {
+        const float* P = P0 + i0 + k;
+        return Shape{P[0], P[N], P[2 * N], P[3 * N], P[4 * N], P[5 * N]};
+    };
+    if (left > 0) {
+        int32_t k_next = record((int32_t)threadIdx.x);
+        Shape next = shape(k_next);
+        for (int32_t base = 0; base < left; base += kFlowThreads) {
+            const int32_t at = base + (int32_t)threadIdx.x, k = k_next;
+            const Shape g = next;
+            const bool done = !open && at < left && labelled(k);
+            k_next = record(at + kFlowThreads);
+            next = shape(k_next);
+            const bool keep = at < left && flow_may_hit(V, rn2, g, tw, th, tmot) && !done;
+            append(keep, k, s_rec, &s_count);
+        }
     }
     __syncthreads();
     // ---- phase 2
@@ -1276,8 +1317,11 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
         const int64_t want = ceil_div(v->n_gv, kFlowFill * kFlowThreads);
         const int32_t recs = kFlowThreads * (int32_t)imin(want, kFlowRecs / kFlowThreads);
         const int64_t per = ceil_div(ceil_div(v->n_gauss, recs), 8);
+        // Groups of one or two rounds run beside each other and see no labels yet (collecting
+        // there: 30 views of 72 k Gaussians 139 / 142 us, 2 of 432 k 107 / 110).
+        const int32_t open = 8 * per * v->n_views > 2 * kFlowFill;
         k_flow_mask<<<(unsigned)(8 * per * v->n_views), kFlowThreads, 0, s>>>(
-            v->d_views, v->n_views, v->channels, v->n_gauss, recs, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h,
+            v->d_views, v->n_views, v->channels, v->n_gauss, recs, open, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h,
             params, masks, tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
     }
     if (dyn_texel && HW > 0)
