@@ -531,28 +531,47 @@ __device__ __forceinline__ uint64_t first_bytes(uint64_t w, int32_t n) {
 
 // A tile is 256 pixels, 32 runs of eight: half a wave per tile, one run per lane.
 // The tile's byte has a bit per cell of 8 x 4 pixels (row-major) that holds motion.
+// The view is looked up once per group and again only for tiles past its end.  On
+// many tiles a lane takes TILES of them, so that as many loads are in flight (50 views
+// of 1024 x 768, 39 MB of masks: 40 us with a tile and a look-up per lane, 25 with four);
+// few tiles spread over more groups instead (4 views of 800 x 600 with four tiles per
+// lane: 1.6 us more).
+constexpr int kMotionTiles = 4;
+constexpr int64_t kMotionMany = 32768;
+template <int TILES>
 __global__ __launch_bounds__(256) void k_tile_motion(const ViewDev* __restrict__ views, int nv, int64_t n_tiles,
                                                      int64_t n_pixels, int32_t tw,
                                                      const uint8_t* __restrict__ masks, uint8_t* __restrict__ tmot) {
-    const int64_t tile = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
+    const int64_t tile0 = (int64_t)blockIdx.x * (8 * TILES);
     const int32_t runs = tw / 8, th = 256 / tw;
-    bool any = false;
-    if (tile < n_tiles) {
-        const ViewDev& V = views[find_view_by_tile(views, nv, tile)];
-        const int64_t local = tile - V.tile_base;
-        const int32_t ty = (int32_t)(local / V.TX), tx = (int32_t)(local - (int64_t)ty * V.TX);
-        const int32_t k = (int32_t)(threadIdx.x % 32);
-        const int32_t x = tx * tw + (k % runs) * 8, y = ty * th + k / runs;
-        if (x < V.W && y < V.H)
-            any = first_bytes(mask8(masks, V.pix_base + (int64_t)y * V.W + x, n_pixels), V.W - x) != 0;
+    const int32_t v0 = find_view_by_tile(views, nv, tile0);
+    const int64_t next = v0 + 1 < nv ? views[v0 + 1].tile_base : n_tiles;
+    const int32_t k = (int32_t)(threadIdx.x % 32);
+    bool any[TILES];
+#pragma unroll
+    for (int q = 0; q < TILES; q++) {
+        const int64_t tile = tile0 + q * 8 + threadIdx.x / 32;
+        any[q] = false;
+        if (tile < n_tiles) {
+            const ViewDev& V = views[tile < next ? v0 : find_view_by_tile(views, nv, tile)];
+            const uint32_t local = (uint32_t)(tile - V.tile_base), ty = local / (uint32_t)V.TX;
+            const int32_t x = (int32_t)(local - ty * (uint32_t)V.TX) * tw + (k % runs) * 8;
+            const int32_t y = (int32_t)ty * th + k / runs;
+            if (x < V.W && y < V.H)
+                any[q] = first_bytes(mask8(masks, V.pix_base + (int64_t)y * V.W + x, n_pixels), V.W - x) != 0;
+        }
     }
-    const uint64_t b = __ballot(any);
-    uint32_t h = (uint32_t)(threadIdx.x & 32 ? b >> 32 : b);
-    h |= h >> runs;             // four rows of runs into one
-    h |= h >> (2 * runs);
-    uint32_t cells = 0;
-    for (int32_t r = 0; r < th / 4; r++) cells |= ((h >> (4 * r * runs)) & ((1u << runs) - 1u)) << (r * runs);
-    if (tile < n_tiles && threadIdx.x % 32 == 0) tmot[tile] = (uint8_t)cells;
+#pragma unroll
+    for (int q = 0; q < TILES; q++) {
+        const int64_t tile = tile0 + q * 8 + threadIdx.x / 32;
+        const uint64_t b = __ballot(any[q]);
+        uint32_t h = (uint32_t)(threadIdx.x & 32 ? b >> 32 : b);
+        h |= h >> runs;             // four rows of runs into one
+        h |= h >> (2 * runs);
+        uint32_t cells = 0;
+        for (int32_t r = 0; r < th / 4; r++) cells |= ((h >> (4 * r * runs)) & ((1u << runs) - 1u)) << (r * runs);
+        if (tile < n_tiles && k == 0) tmot[tile] = (uint8_t)cells;
+    }
 }
 
 // Whether a cell under the pixels [x0, x1] x [y0, y1] (inside the view) holds motion.
@@ -1308,9 +1327,12 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
                             uint64_t* counters, hipStream_t s) {
     const int64_t nfn = (int64_t)v->frames * v->n_gauss;
     if (nfn > 0) k_fill_u8<<<(unsigned)ceil_div(nfn, 256), 256, 0, s>>>(dyn_gauss, nfn);
-    if (v->n_tiles > 0)
-        k_tile_motion<<<(unsigned)ceil_div(v->n_tiles, 8), 256, 0, s>>>(
+    if (v->n_tiles > 0) {
+        const int tiles = v->n_tiles > kMotionMany ? kMotionTiles : 1;
+        auto* kernel = tiles == 1 ? k_tile_motion<1> : k_tile_motion<kMotionTiles>;
+        kernel<<<(unsigned)ceil_div(v->n_tiles, 8 * tiles), 256, 0, s>>>(
             v->d_views, v->n_views, v->n_tiles, v->n_pixels, v->tiling.tile_w, masks, tile_motion);
+    }
     if (v->n_gv > 0) {
         // Few records: smaller chunks, so that they spread over the chip (2,048 Gaussians per
         // group / this rule: 10 views of 12,800 Gaussians 109 / 49 us, 30 of 90,000 176 / 146)
