@@ -208,21 +208,6 @@ __device__ __forceinline__ int64_t block_sum_1024(int64_t c, int64_t* s) {
     return t;
 }
 
-// What the passes of a sort count on, cleared ahead of them by an earlier kernel:
-// status words, digit counts, and the error and finished-group words after err.
-struct SortClear {
-    unsigned long long* status = nullptr;
-    int64_t status_words = 0;
-    uint32_t* hist = nullptr;
-    int32_t hist_words = 0;
-    int32_t* err = nullptr;
-    __device__ __forceinline__ void run(int64_t words, int64_t i0, int64_t stride) const {
-        for (int64_t i = i0; i < words; i += stride) status[i] = 0ull;
-        for (int64_t i = i0; i < hist_words; i += stride) hist[i] = 0u;
-        if (i0 < 2 && err) err[i0] = 0;
-    }
-};
-
 // The kernels that walk the records (k_valid_count, k_compact) take a
 // group's kBlk records with four per lane, 64 apart, so that four loads are in flight in
 // each; with one, in groups of 1,024 threads, they waited on it and on the barriers of
@@ -759,6 +744,7 @@ __global__ __launch_bounds__(256) void k_os_hist(const uint32_t* __restrict__ ke
     }
     __syncthreads();
     const int64_t n = *n_ptr;
+    if (n == 0) return;       // the passes read nothing either
     for (int64_t base = (int64_t)blockIdx.x * 256 * KPT; base < n; base += (int64_t)gridDim.x * 256 * KPT)
         os_count<BITS, UNIFORM, KPT>(keys, base, n, 0u, passes, s[threadIdx.x >> 6]);
     __syncthreads();
@@ -1281,7 +1267,8 @@ hipError_t launch_tile_order(const int32_t* ranges, int64_t n_tiles, int32_t* cn
 // The same LSD passes for other parts of the library: n (read on the device,
 // at most cap) uint32 keys whose low `bits` bits matter, with int32 values,
 // ping-ponged between the two buffer pairs; *out_keys / *out_vals name the
-// pair that holds the result.
+// pair that holds the result.  cleared: an earlier kernel has run the words'
+// SortClear (sort_pairs_clear), where there is anything to sort.
 namespace {
 }  // namespace
 
@@ -1289,11 +1276,17 @@ size_t sort_pairs_ws_bytes(int64_t cap, int bits) {
     return os_ws_bytes(cap, digit_plan(bits, kDepthDigitBits));
 }
 
+SortClear sort_pairs_clear(int64_t cap, int bits, void* ws) {
+    const DigitPlan pl = digit_plan(bits, kDepthDigitBits);
+    return sort_clear(os_carve(cap, pl, (char*)ws), pl);
+}
+
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, const int64_t* n_dev,
-                      int64_t cap, int bits, void* ws, uint32_t** out_keys, int32_t** out_vals, hipStream_t s) {
+                      int64_t cap, int bits, void* ws, bool cleared, uint32_t** out_keys, int32_t** out_vals,
+                      hipStream_t s) {
     const DigitPlan pl = digit_plan(bits, kDepthDigitBits);
     const OsWs w = os_carve(cap, pl, (char*)ws);
-    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, w, true, false, false, false, s);
+    const hipError_t e = onesweep_sort(pl, keys, vals, keys_alt, vals_alt, n_dev, cap, w, true, false, cleared, false, s);
     const bool even = pl.passes % 2 == 0;
     *out_keys = even ? keys : keys_alt;
     *out_vals = even ? vals : vals_alt;

@@ -75,6 +75,21 @@ hipError_t scan_i32(const int32_t* in, int32_t* out, const int64_t* n_dev, int64
                     int64_t* total_out, int64_t* block_tmp, hipStream_t s);
 constexpr int64_t kScanTmpWords = kScanBlocks + 1;   // int64 scratch words a scan needs
 
+// What the passes of a sort count on, cleared ahead of them by an earlier kernel:
+// status words, digit counts, and the error and finished-group words after err.
+struct SortClear {
+    unsigned long long* status = nullptr;
+    int64_t status_words = 0;
+    uint32_t* hist = nullptr;
+    int32_t hist_words = 0;
+    int32_t* err = nullptr;
+    __device__ __forceinline__ void run(int64_t words, int64_t i0, int64_t stride) const {
+        for (int64_t i = i0; i < words; i += stride) status[i] = 0ull;
+        for (int64_t i = i0; i < hist_words; i += stride) hist[i] = 0u;
+        if (i0 < 2 && err) err[i0] = 0;
+    }
+};
+
 // Arrays of at most kScanShort values: one launch instead of three, and two
 // arrays of the same length in it (two arrays of a few counts 4 us against 17; at
 // 14,300 counts one work-group takes 26 us against 27, and 16 against 13 for one).
@@ -162,8 +177,9 @@ hipError_t launch_bin_sort(const pg_views* v, const pg_bin* bins, const pg_tile_
 
 // stable sort of (uint32 key, int32 value) pairs (binsort.hip)
 size_t sort_pairs_ws_bytes(int64_t cap, int bits);
+SortClear sort_pairs_clear(int64_t cap, int bits, void* ws);
 hipError_t sort_pairs(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, const int64_t* n_dev,
-                      int64_t cap, int bits, void* ws, uint32_t** out_keys, int32_t** out_vals, hipStream_t s);
+                      int64_t cap, int bits, void* ws, bool cleared, uint32_t** out_keys, int32_t** out_vals, hipStream_t s);
 
 // render.hip
 hipError_t launch_render_fwd(const pg_views* v, const pg_splat* splats, const int32_t* values,

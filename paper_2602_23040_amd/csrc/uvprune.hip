@@ -20,7 +20,9 @@
 // from the start of its run.  Without the flag they find no pairs and each of
 // their launches ends at once (about 2 us).  Maps with more than kUvDense
 // Gaussians a pixel go to the sorts alone.  1.26 M Gaussians of two frames on a
-// 512 x 256 map: 311 -> 239 us for the call with its fetch.
+// 512 x 256 map: 311 -> 239 us for the call with its fetch, and 214 with one-launch
+// list places and the sorts' words cleared by the kernels before them (4 k to 90 k
+// Gaussians: 100 -> 81).
 #include "pg_internal.h"
 
 namespace pg {
@@ -40,11 +42,20 @@ __device__ __forceinline__ uint32_t desc_key(float x) {
     return ~asc;
 }
 
-// cnt[0]: records; cnt[1]: records to sort (lists: none until a list is too long).
-__global__ void k_uv_count(const int64_t* __restrict__ n_dev, int64_t n_cap, int32_t F, int lists,
-                           int64_t* __restrict__ cnt) {
-    cnt[0] = (int64_t)F * imin(*n_dev, n_cap);
-    cnt[1] = lists ? 0 : cnt[0];
+// cnt[0]: records; cnt[1]: records to sort (lists: none until a list is too long);
+// cnt[2]: list entries given out.  And the pixels' counts, cleared.
+__global__ __launch_bounds__(kT) void k_uv_init(const int64_t* __restrict__ n_dev, int64_t n_cap, int32_t F, int lists,
+                                                int64_t* __restrict__ cnt, int32_t* __restrict__ count,
+                                                int64_t pixels) {
+    const int64_t i0 = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (i0 == 0) {
+        const int64_t n = (int64_t)F * imin(*n_dev, n_cap);
+        cnt[0] = n;
+        cnt[1] = lists ? 0 : n;
+        cnt[2] = 0;
+    }
+    if (lists)
+        for (int64_t i = i0; i < pixels; i += (int64_t)gridDim.x * kT) count[i] = 0;
 }
 
 __global__ __launch_bounds__(kT) void k_uv_key(const float* __restrict__ params, const int64_t* __restrict__ n_dev,
@@ -86,34 +97,69 @@ __global__ __launch_bounds__(kT) void k_uv_key(const float* __restrict__ params,
     }
 }
 
+// Each pixel's list: its first entry and its length.  Which pixels' lists lie first does
+// not matter, so a group of pixels takes its entries from a running count and no scan over
+// all pixels is needed (three launches).
+constexpr int kPlace = 1024;
+__global__ __launch_bounds__(kPlace) void k_uv_place(int64_t* __restrict__ cnt, const int32_t* __restrict__ count,
+                                                     int64_t pixels, int2* __restrict__ place) {
+    __shared__ int32_t s_wave[kPlace / 64];
+    __shared__ int32_t s_base;
+    if (cnt[1]) return;
+    const int64_t p = (int64_t)blockIdx.x * kPlace + threadIdx.x;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int32_t c = p < pixels ? count[p] : 0;
+    int32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t x = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += x;
+    }
+    if (lane == 63) s_wave[wid] = incl;
+    __syncthreads();
+    int32_t before = 0, total = 0;
+    for (int w = 0; w < kPlace / 64; w++) {
+        if (w < wid) before += s_wave[w];
+        total += s_wave[w];
+    }
+    if (threadIdx.x == 0)
+        s_base = total ? (int32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&cnt[2]), (unsigned long long)total) : 0;
+    __syncthreads();
+    if (p < pixels) place[p] = make_int2(s_base + before + incl - c, c);
+}
+
 // The lists: opacity key (high) and Gaussian of every valid record at its place, so
 // that entries in ascending order are in rank order (ties by ascending id).
 __global__ __launch_bounds__(kT) void k_uv_scatter(const int64_t* __restrict__ cnt, int64_t n_cap, int32_t M,
                                                    int32_t Nv, const uint32_t* __restrict__ okey,
                                                    const int32_t* __restrict__ oval, const int32_t* __restrict__ uv,
-                                                   const int32_t* __restrict__ slot, const int32_t* __restrict__ start,
+                                                   const int32_t* __restrict__ slot, const int2* __restrict__ place,
                                                    uint64_t* __restrict__ list) {
     const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (j >= cnt[0] || cnt[1]) return;
     const int32_t g = oval[j], u = uv[g];
     if (u < 0) return;
-    list[(int64_t)start[(g / n_cap) * M * Nv + u] + slot[g]] = (uint64_t)okey[j] << 32 | (uint32_t)g;
+    list[(int64_t)place[(g / n_cap) * M * Nv + u].x + slot[g]] = (uint64_t)okey[j] << 32 | (uint32_t)g;
 }
 
 __global__ __launch_bounds__(kT) void k_uv_list_rank(const int64_t* __restrict__ cnt, int64_t n_cap, int32_t M,
                                                      int32_t Nv, const uint32_t* __restrict__ okey,
                                                      const int32_t* __restrict__ oval, const int32_t* __restrict__ uv,
-                                                     const int32_t* __restrict__ start,
-                                                     const uint64_t* __restrict__ list, int32_t K,
+                                                     const int2* __restrict__ place,
+                                                     const uint64_t* __restrict__ list, int32_t K, SortClear clear,
                                                      int32_t* __restrict__ rank, uint8_t* __restrict__ keep) {
     const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (j >= cnt[0] || cnt[1]) return;
+    if (cnt[1]) {       // left to the sorts: their first one's words
+        clear.run(clear.status_words, j, (int64_t)gridDim.x * kT);
+        return;
+    }
+    if (j >= cnt[0]) return;
     const int32_t g = oval[j], u = uv[g];
     int32_t r = -1;
     if (u >= 0) {
-        const int64_t pix = (g / n_cap) * M * Nv + u;
+        const int2 at = place[(g / n_cap) * M * Nv + u];
         const uint64_t mine = (uint64_t)okey[j] << 32 | (uint32_t)g;
-        const int32_t e0 = start[pix], end = start[pix + 1];
+        const int32_t e0 = at.x, end = at.x + at.y;
         r = 0;
         for (int32_t e = e0; e < end; e += 4) {         // four entries in flight
             uint64_t x[4];
@@ -130,9 +176,10 @@ __global__ __launch_bounds__(kT) void k_uv_list_rank(const int64_t* __restrict__
 // records in opacity order -> (frame, pixel) keys; invalid ones get F M Nv
 __global__ __launch_bounds__(kT) void k_uv_emit(const int32_t* __restrict__ oval, const int64_t* __restrict__ cnt,
                                                 int64_t n_cap, int32_t M, int32_t Nv, int32_t F,
-                                                const int32_t* __restrict__ uv, uint32_t* __restrict__ pkey,
-                                                int32_t* __restrict__ pval) {
+                                                const int32_t* __restrict__ uv, SortClear clear,
+                                                uint32_t* __restrict__ pkey, int32_t* __restrict__ pval) {
     const int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x;
+    if (cnt[0] && clear.err) clear.run(clear.status_words, j, (int64_t)gridDim.x * kT);    // the second sort's words
     if (j >= cnt[0]) return;
     const int32_t g = oval[j];
     const int32_t f = (int32_t)(g / n_cap);
@@ -176,6 +223,7 @@ struct UvWs {
     int64_t* cnt;
     uint32_t *ka, *kb;
     int32_t *va, *vb, *start;
+    int2* place;
     void* sort_ws;
 };
 
@@ -189,12 +237,13 @@ UvWs carve_uv(int64_t n_cap, int32_t F, int32_t M, int32_t Nv, void* ws, size_t*
         return q;
     };
     UvWs w{};
-    w.cnt = (int64_t*)take(16);
+    w.cnt = (int64_t*)take(24);
     w.ka = (uint32_t*)take(n * 4);
     w.va = (int32_t*)take(n * 4);
     w.kb = (uint32_t*)take(n * 4);      // kb and vb together also hold the lists' 8-byte entries
     w.vb = (int32_t*)take(n * 4);
     w.start = (int32_t*)take(((int64_t)F * M * Nv + 1) * 4);
+    w.place = (int2*)take(n_cap <= kUvDense * M * Nv ? (int64_t)F * M * Nv * 8 : 0);
     const int bits = imax(32, key_bits_for((int64_t)F * M * Nv + 1));
     w.sort_ws = take(sort_pairs_ws_bytes(n, bits));
     if (total) *total = off;
@@ -216,38 +265,35 @@ hipError_t launch_uv_prune(const float* params, const int64_t* n_dev, int64_t n_
     const int64_t n = (int64_t)F * n_cap;
     const int64_t pixels = (int64_t)F * M * Nv;
     const bool lists = n_cap <= kUvDense * M * Nv;
-    k_uv_count<<<1, 1, 0, s>>>(n_dev, n_cap, F, lists, w.cnt);
+    k_uv_init<<<lists ? (unsigned)imin(ceil_div(pixels, kT), 1024) : 1u, kT, 0, s>>>(n_dev, n_cap, F, lists, w.cnt,
+                                                                                     w.start, pixels);
     if (n == 0) return hipGetLastError();
     const unsigned grid = (unsigned)ceil_div(n, kT);
+    const int pixel_bits = key_bits_for(pixels + 1);
     hipError_t e = hipSuccess;
-    if (lists) {
-        e = fill_u32(w.start, 0u, pixels + 1, s);
-        if (e != hipSuccess) return e;
-    }
     k_uv_key<<<grid, kT, 0, s>>>(params, n_dev, n_cap, F, C, M, Nv, expected, uv, w.ka, w.va,
                                  lists ? w.start : nullptr, rank, w.cnt);
     if (lists) {
-        // counts -> list starts in place (the scan's scratch is the sorts', which come later)
-        e = scan_i32(w.start, w.start, nullptr, 0, pixels + 1, nullptr, (int64_t*)w.sort_ws, s);
-        if (e != hipSuccess) return e;
-        k_uv_scatter<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, rank, w.start, (uint64_t*)w.kb);
-        k_uv_list_rank<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, w.start, (const uint64_t*)w.kb, K, rank,
-                                             keep);
+        k_uv_place<<<(unsigned)ceil_div(pixels, kPlace), kPlace, 0, s>>>(w.cnt, w.start, pixels, w.place);
+        k_uv_scatter<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, rank, w.place, (uint64_t*)w.kb);
+        k_uv_list_rank<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, w.place, (const uint64_t*)w.kb, K,
+                                           sort_pairs_clear(n, 32, w.sort_ws), rank, keep);
     }
     // records to sort: all of them, or none when the lists have ranked them
     const int64_t* left = w.cnt + 1;
     uint32_t* ok;
     int32_t* ov;
-    e = sort_pairs(w.ka, w.va, w.kb, w.vb, left, n, 32, w.sort_ws, &ok, &ov, s);
+    e = sort_pairs(w.ka, w.va, w.kb, w.vb, left, n, 32, w.sort_ws, lists, &ok, &ov, s);
     if (e != hipSuccess) return e;
     // the pixel keys go to the pair the opacity order does not occupy
     uint32_t* pk = ok == w.ka ? w.kb : w.ka;
     int32_t* pv = ov == w.va ? w.vb : w.va;
-    k_uv_emit<<<grid, kT, 0, s>>>(ov, left, n_cap, M, Nv, F, uv, pk, pv);
-    const uint32_t sentinel = (uint32_t)((int64_t)F * M * Nv);
+    k_uv_emit<<<grid, kT, 0, s>>>(ov, left, n_cap, M, Nv, F, uv,
+                                  lists ? sort_pairs_clear(n, pixel_bits, w.sort_ws) : SortClear{}, pk, pv);
+    const uint32_t sentinel = (uint32_t)pixels;
     uint32_t* sk;
     int32_t* sv;
-    e = sort_pairs(pk, pv, ok, ov, left, n, key_bits_for((int64_t)sentinel + 1), w.sort_ws, &sk, &sv, s);
+    e = sort_pairs(pk, pv, ok, ov, left, n, pixel_bits, w.sort_ws, lists, &sk, &sv, s);
     if (e != hipSuccess) return e;
     k_uv_start<<<grid, kT, 0, s>>>(sk, left, w.start);
     k_uv_rank<<<grid, kT, 0, s>>>(sk, sv, left, w.start, sentinel, K, rank, keep);
