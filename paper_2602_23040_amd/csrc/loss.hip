@@ -33,19 +33,22 @@
 //   dS/dx_q = (w * P_a)_q + x_q (w * (2 P_c + P_e))_q - d_q (w * P_e)_q:
 // no term is a difference of large ones where the images are close, which is
 // where a fit spends its time.
-// x and y are shifted before they are multiplied (E[x~ y~] - a~ b~ with x~ = x - k
+// x, y and d are shifted before they are multiplied (E[x~ y~] - a~ b~ with x~ = x - k
 // equals the covariance, padding included, since the window sums to 1), which
-// keeps FP32 cancellation small.  Each lane's shift is a pixel of its own column and
-// moves every kRebase rows; the windows under way are then re-expressed in the new
-// one.  (One shift for the whole strip spares 33 instructions a row and loses a
-// digit in flat areas beside texture.)  Three waves, one per channel, share a work-group; per-strip sums
+// keeps FP32 cancellation small: d too, which is constant where both images are flat
+// (with d as it is, a flat 0.2 against a flat 0.8 had 1e-4 of error in the SSIM term,
+// 2e-8 shifted, and one view's loss at 2.0 against 0.5 5e-4).  Each lane's shift is a
+// pixel of its own column, eight rows ahead, and moves every kRebase rows; the windows
+// under way are then re-expressed in the new one.  (With 32 rows bands of flat colours
+// up to 2 have seven times the error of 16.  One shift for the whole strip spares 33
+// instructions a row and loses a digit in flat areas beside texture.)  Three waves, one per channel, share a work-group; per-strip sums
 // of S and |I - T| (FP64) go to a small partial array that k_photo_final reduces.
 //
 // Bound by FP32 VALU issue, about 300 instructions per lane and row: the strip's
 // 64 lanes give 54 columns and its rows run 20 ahead of the first output, 1.3
-// times the work without halos.  The form before it (32 x 32 blocks in LDS, every
-// tap of both passes read from there) took 795 us for 16 views of 1024x768 and
-// 2,338 for 50; this one 494 and 1,273, with half the error against FP64.
+// times the work without halos.  16 views of 1024x768: 754 us by 32 x 32 blocks in
+// LDS (every tap of both passes read from there), 433 by strips (414 before d was
+// shifted); error against FP64 on images 0.05 from their targets 2e-6 and 7.7e-7.
 #include "pg_internal.h"
 
 namespace pg {
@@ -58,7 +61,7 @@ constexpr int kLanes = 64;
 constexpr int kStripCols = kLanes - 2 * kR; // output columns of a strip: a wave less the window's reach on both sides
 constexpr int64_t kStripFill = 1024;        // strips (of three waves) that fill the chip
 constexpr int kChannels = 3;
-constexpr int kRebase = 32;                 // rows between shifts of the base
+constexpr int kRebase = 16;                 // rows between shifts of the base
 constexpr int kB = 32;                      // output block side
 constexpr int kIW = kB + 4 * kR;            // input patch side (42 + 10 = 52 with 2 halos)
 constexpr int kMW = kB + 2 * kR;            // partial-map region side (42)
@@ -141,7 +144,7 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
         }
     };
     // running vertical windows: [k] completes after k + 1 more rows
-    float va[2 * kR], vd[2 * kR], vq[2 * kR], vr[2 * kR];      // means of x, d, x y, d^2
+    float va[2 * kR], vd[2 * kR], vq[2 * kR], vr[2 * kR];      // means of x, d, x y, d^2, shifted
     float ga[2 * kR], gf[2 * kR], ge[2 * kR];                  // blurred partial maps
 #pragma unroll
     for (int k = 0; k < 2 * kR; k++) va[k] = vd[k] = vq[k] = vr[k] = ga[k] = gf[k] = ge[k] = 0.f;
@@ -157,22 +160,26 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
         return out;
     };
     double s_sum = 0.0, l1_sum = 0.0;
-    float kx = 0.f, ky = 0.f;
+    float kx = 0.f, kd = 0.f;        // the lane's shifts of x and d (of y: kx - kd)
     const double w_l1 = (double)(1.0f - lambda) * inv_n, w_ssim = (double)lambda * inv_n;
     auto rebase = [&](int32_t r) __attribute__((always_inline)) {
         const int64_t p = (int64_t)min(max(r + kRebase / 2, 0), H - 1) * W + min(max(cx, 0), W - 1);
-        const float nx = X[p], ny = Y[p];
-        const float dx = nx - kx, dy = ny - ky;
-        // sum w (x~ - dx)(y~ - dy) = sum w x~ y~ - dx sum w y~ - dy sum w x~ + dx dy sum w
+        const float nx = X[p], nd = nx - Y[p];
+        const float dx = nx - kx, dd = nd - kd, dy = dx - dd;
+        // sum w (x~ - dx)(y~ - dy) = sum w x~ y~ - dx sum w y~ - dy sum w x~ + dx dy sum w,
+        // and the square of d~ alike
         float wsum = 0.f;      // weights taken by window k
 #pragma unroll
         for (int k = 2 * kR - 1; k >= 0; k--) {
             wsum += win.w[2 * kR - 1 - k];
-            const float wx = fmaf(-kx, wsum, va[k]), wy = fmaf(-ky, wsum, va[k] - vd[k]);
+            const float wx = va[k], wd = vd[k], wy = wx - wd;
             vq[k] = fmaf(dx, fmaf(dy, wsum, -wy), fmaf(-dy, wx, vq[k]));
+            vr[k] = fmaf(dd, fmaf(dd, wsum, -2.0f * wd), vr[k]);
+            vd[k] = fmaf(-dd, wsum, wd);
+            va[k] = fmaf(-dx, wsum, wx);
         }
         kx = nx;
-        ky = ny;
+        kd = nd;
     };
     // input row r: the windows it completes (row r - 5)
     float ma, md, mq, mr, xv = 0.f, yv = 0.f;
@@ -187,10 +194,10 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int j = 0; j < kK; j++) {
             const float2 v = s_in[lane + j];
-            const float w = win.w[j], d = v.x - v.y;
-            ha = fmaf(w, v.x, ha);
+            const float w = win.w[j], x = v.x - kx, d = (v.x - v.y) - kd;
+            ha = fmaf(w, x, ha);
             hd = fmaf(w, d, hd);
-            hq = fmaf(w * (v.x - kx), v.y - ky, hq);
+            hq = fmaf(w * x, x - d, hq);
             hr = fmaf(w, d * d, hr);
         }
         ma = push(va, ha);
@@ -204,8 +211,8 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
         const bool out = own && r2 >= y0;
         float pa = 0.f, pf = 0.f, pe = 0.f;
         if (in_map && r1 >= 0 && r1 < H) {
-            const float a = ma, b = a - md, m2 = md * md;
-            const float sd = mr - m2, sxy = mq - (a - kx) * (b - ky);
+            const float sd = mr - md * md, sxy = mq - ma * (ma - md);      // of the shifted means
+            const float a = ma + kx, m = md + kd, b = a - m, m2 = m * m;
             const float N1 = 2.0f * a * b + kC1, N2 = 2.0f * sxy + kC2;
             const float D1 = N1 + m2, D2 = N2 + sd;
             const float DD = D1 * D2, rcp = __builtin_amdgcn_rcpf(DD);
@@ -213,7 +220,7 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
             const float S = N1 * N2 * iD, U = fmaf(N1, sd, m2 * D2) * iD;     // S, 1 - S
             pe = 2.0f * N1 * iD;
             pf = pe * sd * (D1 * iD);
-            pa = 2.0f * iD * fmaf(N2 - N1, fmaf(a, U, -md), -(a * S) * (sd - m2));
+            pa = 2.0f * iD * fmaf(N2 - N1, fmaf(a, U, -m), -(a * S) * (sd - m2));
             if (own && r1 >= y0 && r1 < y1) s_sum += (double)S;
         }
         s_map[kR + lane] = make_float4(pa, pf, pe, 0.f);
