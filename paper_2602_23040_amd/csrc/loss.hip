@@ -164,7 +164,11 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
     const double w_l1 = (double)(1.0f - lambda) * inv_n, w_ssim = (double)lambda * inv_n;
     auto rebase = [&](int32_t r) __attribute__((always_inline)) {
         const int64_t p = (int64_t)min(max(r + kRebase / 2, 0), H - 1) * W + min(max(cx, 0), W - 1);
-        const float nx = X[p], nd = nx - Y[p];
+        float nx = X[p], nd = nx - Y[p];
+        // a pixel that is not finite spoils the windows that hold it; as a shift it would spoil all
+        const bool finite = fabsf(nx) < INFINITY && fabsf(nd) < INFINITY;
+        nx = finite ? nx : kx;
+        nd = finite ? nd : kd;
         const float dx = nx - kx, dd = nd - kd, dy = dx - dd;
         // sum w (x~ - dx)(y~ - dy) = sum w x~ y~ - dx sum w y~ - dy sum w x~ + dx dy sum w,
         // and the square of d~ alike
