@@ -252,7 +252,10 @@ __global__ __launch_bounds__(kChannels * kLanes) __attribute__((amdgpu_waves_per
     for (int32_t c0 = first; c0 < last; c0 += kRebase) {
         rebase(c0);
         int32_t r = c0;
-        for (; r < y0; r++) input_row(r);                  // windows of the first map row still under way
+        for (; r < y0; r++) {                              // windows of the first map row still under way
+            input_row(r);
+            wave_lds_order();      // its reads before the next row's store (in the rows below s_map's stand between)
+        }
         for (; r < min(c0 + kRebase, last); r++) {
             input_row(r);
             output_row(r);
