@@ -110,10 +110,25 @@ __global__ void k_status(const int32_t* __restrict__ overflow, const int64_t* __
     host[1] = *n_inst;
 }
 
+// Whether a kernel on the current device may read p: its own device memory.  (The null
+// stream is the current device's, whichever device the words are on, so its launch is
+// no check.)
+bool on_current_device(const void* p) {
+    hipPointerAttribute_t a;
+    int device = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || hipGetDevice(&device) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 // The two words by one kernel and one wait.  False where that is not possible
-// (no pinned pair, a stream of another device): the caller then copies them.
+// (words that are not the current device's, no pinned pair, a stream of another
+// device): the caller then copies them.
 bool status_words(const int32_t* overflow_dev, const int64_t* n_inst_dev, hipStream_t s, int32_t* ovf, int64_t* need,
                   hipError_t* e) {
+    if (!on_current_device(overflow_dev) || !on_current_device(n_inst_dev)) return false;
     int64_t* host = g_status_words.take();
     if (!host) return false;
     void* args[] = {&overflow_dev, &n_inst_dev, &host};
