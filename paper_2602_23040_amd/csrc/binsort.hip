@@ -174,7 +174,9 @@ SortWs carve(const pg_views* v, int64_t cap, void* ws, size_t* total) {
     w.tv_alt = (int32_t*)take(imax(cap, 1) * 4);
     w.rec_seg = (SortSeg*)take(pl.segs * sizeof(SortSeg));
     w.inst_seg = (SortSeg*)take(pl.segs * sizeof(SortSeg));
-    w.os = take(std::max(os_ws_bytes(ngv, pl.depth, pl.segs), os_ws_bytes(cap, pl.tile, pl.segs)));
+    // (views apart may sort by fewer tile digits than the one sort of a smaller table or capacity)
+    w.os = take(std::max({os_ws_bytes(ngv, pl.depth, pl.segs), os_ws_bytes(cap, pl.tile, pl.segs),
+                          os_ws_bytes(cap, digit_plan(v->key_bits, kTileDigitBits))}));
     const int64_t order_words = ceil_div(imax(v->n_tiles, 1), kOrderBlk) * kOrderClasses;
     w.order_cnt = (int32_t*)take(order_words * 4);
     w.order_base = (int32_t*)take(order_words * 4);
@@ -1009,10 +1011,14 @@ OsWs os_layout(int64_t cap, DigitPlan pl, const SortSeg* segs, int32_t n_segs, c
     if (bytes) *bytes = off;
     return w;
 }
+// Bytes for any sort of at most cap pairs: small radix tiles need four times the status
+// words of large ones, so the largest of the layouts up to cap (a workspace sized once for
+// the largest sort serves the smaller ones).
 size_t os_ws_bytes(int64_t cap, DigitPlan pl, int32_t segs) {
-    size_t bytes = 0;
+    size_t bytes = 0, small = 0;
     os_layout(cap, pl, nullptr, segs, nullptr, &bytes);
-    return bytes;
+    os_layout(imin(cap, kSmallSort), pl, nullptr, 0, nullptr, &small);
+    return std::max(bytes, small);
 }
 OsWs os_carve(int64_t cap, DigitPlan pl, char* p, const SortSeg* segs = nullptr, int32_t n_segs = 0) {
     return os_layout(cap, pl, segs, n_segs, p, nullptr);

@@ -243,7 +243,7 @@ UvWs carve_uv(int64_t n_cap, int32_t F, int32_t M, int32_t Nv, void* ws, size_t*
     w.kb = (uint32_t*)take(n * 4);      // kb and vb together also hold the lists' 8-byte entries
     w.vb = (int32_t*)take(n * 4);
     w.start = (int32_t*)take(((int64_t)F * M * Nv + 1) * 4);
-    w.place = (int2*)take(n_cap <= kUvDense * M * Nv ? (int64_t)F * M * Nv * 8 : 0);
+    w.place = (int2*)take((int64_t)F * M * Nv * 8);     // also where lists are not tried: fewer Gaussians need no more
     const int bits = imax(32, key_bits_for((int64_t)F * M * Nv + 1));
     w.sort_ws = take(sort_pairs_ws_bytes(n, bits));
     if (total) *total = off;
