@@ -493,7 +493,7 @@ pg_status pg_project_bwd(const pg_views* v, const float* params, const pg_splat*
     if (accumulate != 0 && accumulate != 1) return invalid("accumulate must be 0 or 1");
     if (inst_capacity < 0 || inst_capacity > INT32_MAX) return invalid("inst_capacity must be in [0, 2^31 - 1]");
     hipStream_t s = (hipStream_t)stream;
-    PG_CHECK_HIP(launch_slot_sum(v, bins, inst_first, n_inst_dev, inst_capacity, inst_grad, grad2d, s),
+    PG_CHECK_HIP(launch_slot_sum(v, inst_first, n_inst_dev, inst_capacity, inst_grad, grad2d, s),
                  "pg_project_bwd (slot sums)");
     PG_CHECK_HIP(launch_project_bwd(v, params, splats, grad2d, gauss_texel, dynamic_mask, H, W, dL_datlas, accumulate,
                                     s),
@@ -522,7 +522,7 @@ pg_status pg_backward(const pg_views* v, const float* params, const pg_splat* sp
     PG_CHECK_HIP(launch_render_bwd(v, splats, tiles, values, tile_ranges, tile_order, inst_first, tile_entries, entries,
                                    n_contrib, bg, final_T, dL_dimage, n_inst_dev, inst_capacity, inst_grad, nullptr, s),
                  "pg_backward (compositing adjoint)");
-    PG_CHECK_HIP(launch_slot_sum(v, bins, inst_first, n_inst_dev, inst_capacity, inst_grad, grad2d, s),
+    PG_CHECK_HIP(launch_slot_sum(v, inst_first, n_inst_dev, inst_capacity, inst_grad, grad2d, s),
                  "pg_backward (slot sums)");
     PG_CHECK_HIP(launch_project_bwd(v, params, splats, grad2d, gauss_texel, dynamic_mask, H, W, dL_datlas, accumulate,
                                     s),

@@ -52,7 +52,7 @@ int64_t n_blocks(const pg_views* v) { return imax(ceil_div(v->n_gv, kBlk), 1); }
 struct DigitPlan {
     int passes, digit;      // LSD passes of equal width digit bits
 };
-constexpr int kOsMaxBits = 9;                // digit width the radix pass kernels are built for
+constexpr int kOsMaxBits = 8;                // digit width the radix pass kernels are built for
 constexpr int kDepthDigitBits = 8, kDepthPasses = 4;   // digit width caps of the record (depth) and instance (tile) sorts
 constexpr int kTileDigitBits = 7;            // 18-bit tile ids: 3 x 6 bits; 19-21 bits: 3 x 7 instead of 4 x 5
 
@@ -1054,8 +1054,11 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
     if (!counted) switch (pl.digit) {
 #define PG_HIST_AS(B, U, K) \
     k_os_hist<B, U, K><<<hgrid, 256, 0, s>>>(ka, n_ptr, pl.passes, w.hist, w.uni, finished)
-#define PG_HIST_SEG(B) \
-    k_os_hist_seg<B, kSortItems><<<hgrid, 256, 0, s>>>(ka, n_ptr, w.segs, w.n_segs, pl.passes, w.hist)
+// (views apart count tile digits only: their depth digits are counted in the compaction)
+#define PG_HIST_SEG(B)                                                     \
+    if (B > kTileDigitBits) return hipErrorInvalidValue;                   \
+    k_os_hist_seg<(B < kTileDigitBits ? B : kTileDigitBits), kSortItems>   \
+        <<<hgrid, 256, 0, s>>>(ka, n_ptr, w.segs, w.n_segs, pl.passes, w.hist)
 #define PG_HIST(B)                                                  \
     case B:                                                         \
         if (w.n_segs) {                                             \
@@ -1068,7 +1071,7 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
             else PG_HIST_AS(B, false, kSortItems);                  \
         }                                                           \
         break;
-        PG_HIST(1) PG_HIST(2) PG_HIST(3) PG_HIST(4) PG_HIST(5) PG_HIST(6) PG_HIST(7) PG_HIST(8) PG_HIST(9)
+        PG_HIST(1) PG_HIST(2) PG_HIST(3) PG_HIST(4) PG_HIST(5) PG_HIST(6) PG_HIST(7) PG_HIST(8)
 #undef PG_HIST
 #undef PG_HIST_AS
 #undef PG_HIST_SEG
@@ -1092,7 +1095,7 @@ hipError_t onesweep_sort(DigitPlan pl, uint32_t* ka, int32_t* va, uint32_t* kb, 
         else if (small) PG_PASS_AS(B, kSmallItems, false); \
         else PG_PASS_AS(B, kSortItems, false);             \
         break;
-            PG_PASS(1) PG_PASS(2) PG_PASS(3) PG_PASS(4) PG_PASS(5) PG_PASS(6) PG_PASS(7) PG_PASS(8) PG_PASS(9)
+            PG_PASS(1) PG_PASS(2) PG_PASS(3) PG_PASS(4) PG_PASS(5) PG_PASS(6) PG_PASS(7) PG_PASS(8)
 #undef PG_PASS
 #undef PG_PASS_AS
             default: return hipErrorInvalidValue;
@@ -1275,9 +1278,6 @@ hipError_t launch_tile_order(const int32_t* ranges, int64_t n_tiles, int32_t* cn
 // ping-ponged between the two buffer pairs; *out_keys / *out_vals name the
 // pair that holds the result.  cleared: an earlier kernel has run the words'
 // SortClear (sort_pairs_clear), where there is anything to sort.
-namespace {
-}  // namespace
-
 size_t sort_pairs_ws_bytes(int64_t cap, int bits) {
     return os_ws_bytes(cap, digit_plan(bits, kDepthDigitBits));
 }

@@ -161,7 +161,7 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
                             uint8_t* dyn_gauss, const int32_t* texel_gauss, int64_t HW, uint8_t* dyn_texel,
                             uint64_t* counters, hipStream_t s);
 // per-record sums of the instance slots -> grad2d
-hipError_t launch_slot_sum(const pg_views* v, const pg_bin* bins, const int32_t* inst_first,
+hipError_t launch_slot_sum(const pg_views* v, const int32_t* inst_first,
                            const int64_t* n_inst_dev, int64_t cap, const float* inst_grad, float* grad2d,
                            hipStream_t s);
 hipError_t launch_project_bwd(const pg_views* v, const float* params, const pg_splat* splats, float* grad2d,

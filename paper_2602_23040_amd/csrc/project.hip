@@ -1378,7 +1378,7 @@ hipError_t launch_project(const pg_views* v, const float* params, pg_splat* spla
     return hipGetLastError();
 }
 
-hipError_t launch_slot_sum(const pg_views* v, const pg_bin* bins, const int32_t* inst_first,
+hipError_t launch_slot_sum(const pg_views* v, const int32_t* inst_first,
                            const int64_t* n_inst_dev, int64_t cap, const float* inst_grad, float* grad2d,
                            hipStream_t s) {
     if (v->n_gv == 0) return hipSuccess;

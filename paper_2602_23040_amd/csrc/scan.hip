@@ -128,50 +128,45 @@ hipError_t scan_impl(const Tin* in, Tout* out, const int64_t* n_dev, int64_t n_m
     return hipGetLastError();
 }
 
-// Exclusive scans of one or two arrays of n values by one work-group, eight
-// consecutive values per thread and step.
+// Exclusive scans of one or two arrays of n <= kScanShort values by one work-group,
+// consecutive values per thread.
 template <typename Tin>
 __global__ __launch_bounds__(1024) void k_scan_short(ShortScan<Tin> a, ShortScan<Tin> b, int64_t n, SortCount post) {
-    constexpr int kPer = 8;
-    __shared__ int64_t s_wave[16];
+    constexpr int kPer = kScanShort / 1024;
+    __shared__ int64_t s_wave[2][16];
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     for (int which = 0; which < 2; which++) {
         const ShortScan<Tin> sc = which ? b : a;
         if (!sc.in) break;
-        int64_t run = 0;
-        for (int64_t base = 0; base < n; base += 1024 * kPer) {
-            const int64_t i0 = base + (int64_t)t * kPer;
-            int64_t v[kPer], sum = 0;
+        const int64_t i0 = (int64_t)t * kPer;
+        int64_t v[kPer], sum = 0;
 #pragma unroll
-            for (int k = 0; k < kPer; k++) v[k] = i0 + k < n ? (int64_t)sc.in[i0 + k] : 0;
+        for (int k = 0; k < kPer; k++) v[k] = i0 + k < n ? (int64_t)sc.in[i0 + k] : 0;
 #pragma unroll
-            for (int k = 0; k < kPer; k++) sum += v[k];
-            int64_t incl = sum;
+        for (int k = 0; k < kPer; k++) sum += v[k];
+        int64_t incl = sum;
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t u = __shfl_up(incl, o, 64);
-                if (lane >= o) incl += u;
-            }
-            if (lane == 63) s_wave[wid] = incl;
-            __syncthreads();
-            int64_t before = 0, all = 0;
-#pragma unroll
-            for (int w = 0; w < 16; w++) {
-                const int64_t x = s_wave[w];
-                before += w < wid ? x : 0;
-                all += x;
-            }
-            __syncthreads();
-            int64_t x = run + before + incl - sum;
-#pragma unroll
-            for (int k = 0; k < kPer; k++) {
-                if (i0 + k < n) sc.out[i0 + k] = x;
-                x += v[k];
-            }
-            run += all;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t u = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += u;
         }
-        if (t == 0 && sc.total) *sc.total = run;
-        if (t == 0 && which == 0 && post.n_inst) post.finish(run);
+        if (lane == 63) s_wave[which][wid] = incl;
+        __syncthreads();
+        int64_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; w++) {
+            const int64_t x = s_wave[which][w];
+            before += w < wid ? x : 0;
+            all += x;
+        }
+        int64_t x = before + incl - sum;
+#pragma unroll
+        for (int k = 0; k < kPer; k++) {
+            if (i0 + k < n) sc.out[i0 + k] = x;
+            x += v[k];
+        }
+        if (t == 0 && sc.total) *sc.total = all;
+        if (t == 0 && which == 0 && post.n_inst) post.finish(all);
     }
 }
 
