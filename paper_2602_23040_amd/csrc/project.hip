@@ -1244,8 +1244,8 @@ __global__ __launch_bounds__(kSumRecs) void k_slot_sum(const int32_t* __restrict
                                                        float* __restrict__ grad2d) {
     __shared__ float s_g[kSumChunk * kSlotWords];
     __shared__ int64_t s_range[2];
-    __shared__ int64_t s_long[kSumRecs][2];     // slot ranges of the long records
-    __shared__ int32_t s_longs;
+    __shared__ int32_t s_end[kSumRecs];         // the records' last slots + 1, from the group's first
+    __shared__ uint64_t s_skip[kSumRecs / 64];  // which of them are long, or have no slots
     const int64_t g0 = (int64_t)blockIdx.x * kSumRecs;
     const int64_t gv = g0 + threadIdx.x;
     const int64_t glast = imin(g0 + kSumRecs, n_gv) - 1;
@@ -1253,34 +1253,39 @@ __global__ __launch_bounds__(kSumRecs) void k_slot_sum(const int32_t* __restrict
     int64_t first;
     const int32_t nt = slot_range(inst_first, n_inst_dev, cap, gv, n_gv, first);
     const bool is_long = nt > kSumSerial;
-    if (threadIdx.x == 0) s_longs = 0;
+    const int lane = threadIdx.x & 63;
     if (gv == g0) s_range[0] = first;
     if (gv == glast) s_range[1] = first + nt;
+    const uint64_t wave_skip = __ballot(is_long || nt == 0);
+    if (lane == 0) s_skip[threadIdx.x / 64] = wave_skip;
+    const bool any_long = __syncthreads_or(is_long);
+    const int64_t e0 = s_range[0], e1 = s_range[1];
+    s_end[threadIdx.x] = (int32_t)((gv < glast ? first + nt : e1) - e0);
     __syncthreads();
-    if (is_long) {
-        const int32_t at = atomicAdd(&s_longs, 1);      // in any order: the list only says what to pass over
-        s_long[at][0] = first;
-        s_long[at][1] = first + nt;
-    }
-    __syncthreads();
-    const int64_t e1 = s_range[1];
-    const int32_t longs = s_longs;
-    // the next slot from c on that is not a long record's
+    int32_t end[kSumRecs / 64];
+#pragma unroll
+    for (int q = 0; q < kSumRecs / 64; q++) end[q] = s_end[q * 64 + lane];
+    // the next slot from c on that is not a long record's: where c's record is long, the
+    // start of the next one that is not (wave-uniform; each lane knows four records' ends)
     auto next_short = [&](int64_t c) __attribute__((always_inline)) {
-        for (bool moved = longs > 0; moved;) {
-            moved = false;
-            for (int32_t q = 0; q < longs; q++)
-                if (c >= s_long[q][0] && c < s_long[q][1]) {
-                    c = s_long[q][1];
-                    moved = true;
-                }
+        if (!any_long || c >= e1) return c;
+        int32_t r = 0;
+#pragma unroll
+        for (int q = 0; q < kSumRecs / 64; q++) r += __popcll(__ballot(end[q] <= (int32_t)(c - e0)));
+        if (!((s_skip[r / 64] >> (r % 64)) & 1)) return c;
+        int32_t to = kSumRecs;
+#pragma unroll
+        for (int q = kSumRecs / 64 - 1; q >= 0; q--) {
+            const uint64_t from = r <= q * 64 ? ~0ull : (r < q * 64 + 64 ? ~0ull << (r - q * 64) : 0ull);
+            const uint64_t m = ~s_skip[q] & from;
+            if (m) to = q * 64 + __builtin_ctzll(m);
         }
-        return c;
+        return e0 + s_end[to - 1];      // to > r: a record follows one
     };
     float s9[9];
 #pragma unroll
     for (int k = 0; k < 9; k++) s9[k] = 0.0f;
-    for (int64_t c0 = next_short(s_range[0]); c0 < e1; c0 = next_short(c0 + kSumChunk)) {
+    for (int64_t c0 = next_short(e0); c0 < e1; c0 = next_short(c0 + kSumChunk)) {
         const int64_t c1 = imin(e1, c0 + kSumChunk);
         const int32_t nw = (int32_t)((c1 - c0) * kSlotWords);
         __syncthreads();
@@ -1302,7 +1307,6 @@ __global__ __launch_bounds__(kSumRecs) void k_slot_sum(const int32_t* __restrict
             for (int k = 0; k < 9; k++) s9[k] += s_g[u * kSlotWords + k];
         }
     }
-    const int lane = threadIdx.x & 63;
     uint64_t todo = __ballot(is_long);
     while (todo) {
         const int src = __builtin_ctzll(todo);
