@@ -621,7 +621,7 @@ pg_status pg_loss_l1(const float* image, const float* target, int64_t n, float* 
 pg_status pg_photo_workspace_size(const pg_views* v, size_t* bytes) {
     g_error.clear();
     if (!v || !bytes) return invalid("null argument");
-    *bytes = (size_t)(2 * imax(photo_blocks(v), 1)) * sizeof(double);
+    *bytes = (size_t)(2 * imax(photo_sums(v), 1)) * sizeof(double);
     return PG_OK;
 }
 
@@ -632,7 +632,7 @@ pg_status pg_loss_photo(const pg_views* v, const float* image, const float* targ
     if (!loss_dev || !ws) return invalid("null pointer argument");
     if (v->n_pixels > 0 && (!image || !target || !dL_dimage)) return invalid("null pointer argument");
     if (!(lambda_ssim >= 0.0f && lambda_ssim <= 1.0f)) return invalid("lambda_ssim must be in [0, 1]");
-    if (ws_bytes < (size_t)(2 * imax(photo_blocks(v), 1)) * sizeof(double)) {
+    if (ws_bytes < (size_t)(2 * imax(photo_sums(v), 1)) * sizeof(double)) {
         set_error("photometric-loss workspace too small");
         return PG_ERR_WORKSPACE;
     }

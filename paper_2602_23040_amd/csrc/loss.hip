@@ -51,6 +51,9 @@
 // shifted); error against FP64 on images 0.05 from their targets 2e-6 and 7.7e-7.
 #include "pg_internal.h"
 
+#include <algorithm>
+#include <utility>
+
 namespace pg {
 
 namespace {
@@ -59,7 +62,7 @@ constexpr int kR = 5;                       // window half-width
 constexpr int kK = 2 * kR + 1;
 constexpr int kLanes = 64;
 constexpr int kStripCols = kLanes - 2 * kR; // output columns of a strip: a wave less the window's reach on both sides
-constexpr int64_t kStripFill = 1024;        // strips (of three waves) that fill the chip
+constexpr int kStripMin = 16;               // least rows of a strip
 constexpr int kChannels = 3;
 constexpr int kRebase = 16;                 // rows between shifts of the base
 constexpr int kB = 32;                      // output block side
@@ -67,6 +70,7 @@ constexpr int kIW = kB + 4 * kR;            // input patch side (42 + 10 = 52 wi
 constexpr int kMW = kB + 2 * kR;            // partial-map region side (42)
 constexpr int kBlockThreads = 512;          // two output pixels per thread in the last pass
 constexpr int64_t kBlockRound = 512;        // blocks the chip takes at once (two work-groups per CU)
+static_assert(kB % kStripMin == 0 && kB <= kStripCols, "photo_sums");
 constexpr float kC1 = 0.01f * 0.01f, kC2 = 0.03f * 0.03f;
 
 struct Win {
@@ -640,24 +644,46 @@ hipError_t launch_regularisers(const float* params, const int64_t* n_dev, int64_
     return hipGetLastError();
 }
 
-int64_t photo_blocks(const pg_views* v) { return v->n_ssim_blocks; }
+// Pairs of partial sums that hold any table's strips or blocks: strips of kStripMin rows are
+// at most two for each block of 32 x 32 pixels they touch.
+int64_t photo_sums(const pg_views* v) { return (int64_t)(kB / kStripMin) * v->n_ssim_blocks; }
 
-// Rows of a strip: the tallest of 192 and 64 that gives kStripFill strips, else
-// 32 (a strip computes 20 rows more than it gives: 10 %, 31 % and 63 %; for 16
-// views of 1024x768 the three measure 484, 500 and 590 us, for one 1920x1080
-// view 260, 132 and 100).  0: the block kernel.  One round of its work-groups
-// takes 28 us, while a strip cannot be done before its 52 rows, about 56 us
-// (one view of 512x512: 28 / 56 us; four of 640x480: 89 / 79).
+// Rows of a strip, or 0 for the block kernel.  One round of its work-groups takes 27 us,
+// while a strip cannot be done before its rows and the 20 it runs beside them.  Above that
+// the height for which these fits of the measured times (us) are least: 1.6 to 1.75 ns a
+// row when the chip is full (16 views of 1024x768, 32, 64 and 192 rows: 550, 482, 438), and
+// at least a wave's way down its rows, 60 + 0.034 a strip for 52 of them (360: 68, 720: 83,
+// 1,280: 106).  Heights 16 / 32 / 64 / 192, and blocks: 9 views of 256x256 59 / 67 / 96 / 241,
+// 59; 3 of 640x480 74 / 83 / 108 / 242, 75; one of 1920x1080 130 / 103 / 132 / 241, 135; 12 of
+// 512x512 190 / 170 / 137 / 276, 198; 130 of 108x832 643 / 498 / 445 / 490, 836; 30 of 1024x768
+// 1,249 / 969 / 844 / 827, 1,405.  Narrow views leave most of a strip's columns idle: blocks
+// would be faster there (200 views of 64x64 76 against 90), but have a tenth of the digits where
+// images are close.
 int32_t photo_strip_rows(const pg_camera* cams, int32_t n_views) {
-    auto count = [&](int32_t cols, int32_t rows) {
-        int64_t n = 0;
-        for (int32_t v = 0; v < n_views; v++) n += ceil_div(cams[v].width, cols) * ceil_div(cams[v].height, rows);
-        return n;
+    auto count = [&](int32_t v, int32_t cols, int32_t rows) {
+        return ceil_div(cams[v].width, cols) * ceil_div(cams[v].height, rows);
     };
-    if (count(kB, kB) <= kBlockRound) return 0;
-    for (int32_t rows : {192, 64})
-        if (count(kStripCols, rows) >= kStripFill) return rows;
-    return 32;
+    int64_t blocks = 0;
+    for (int32_t v = 0; v < n_views; v++) blocks += count(v, kB, kB);
+    if (blocks <= kBlockRound) return 0;
+    double best = 0.0;
+    int32_t rows = 0;
+    for (const auto& c : {std::make_pair(192, 1.72), {64, 1.62}, {32, 1.75}, {kStripMin, 1.75}}) {
+        double n = 0.0, work = 0.0;
+        int32_t longest = 0;
+        for (int32_t v = 0; v < n_views; v++) {
+            const int32_t steps = std::min(c.first, cams[v].height) + 4 * kR;
+            n += (double)count(v, kStripCols, c.first);
+            work += (double)count(v, kStripCols, c.first) * steps;
+            longest = std::max(longest, steps);
+        }
+        const double t = std::max(1e-3 * c.second * work, (60.0 + 0.034 * n) * longest / 52.0);
+        if (rows == 0 || t < best) {
+            best = t;
+            rows = c.first;
+        }
+    }
+    return rows;
 }
 int64_t photo_groups(int32_t w, int32_t h, int32_t rows) {
     return rows ? ceil_div(w, kStripCols) * ceil_div(h, rows) : ceil_div(w, kB) * ceil_div(h, kB);

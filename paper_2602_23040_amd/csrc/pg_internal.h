@@ -45,7 +45,7 @@ struct pg_views {
     int32_t* d_view_order;     // [n_views] view indices grouped by frame
     int64_t n_ssim_blocks;     // 32 x 32 pixel blocks of all views (photometric loss: its workspace's size)
     int32_t photo_rows;        // rows of the photometric loss's strips (0: 32 x 32 blocks)
-    int64_t n_photo;           // its strips or blocks of all views; at most n_ssim_blocks
+    int64_t n_photo;           // its strips or blocks of all views; at most twice n_ssim_blocks
     int64_t* d_photo_base;     // [n_views] first strip or block of each view
     int64_t* h_tile_base;      // [n_views + 1]
     int64_t* h_pix_base;       // [n_views + 1]
@@ -132,7 +132,7 @@ hipError_t launch_fetch(const float* atlas, const uint8_t* occ, int32_t F, int32
                         int64_t* n_gauss_dev, void* ws, hipStream_t s);
 
 // loss.hip (photometric objective)
-int64_t photo_blocks(const pg_views* v);
+int64_t photo_sums(const pg_views* v);
 int32_t photo_strip_rows(const pg_camera* cams, int32_t n_views);
 int64_t photo_groups(int32_t w, int32_t h, int32_t rows);
 hipError_t launch_photo(const pg_views* v, const float* image, const float* target, float lambda, float* dimg,

@@ -17,7 +17,7 @@ from test_gpu_photo_strips import reference
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [(640, 480), (331, 257), (1024, 200), (54, 33), (5, 400)]     # more than 512 blocks: strips
+SIZES = [(640, 480), (331, 257), (1024, 200), (54, 33), (5, 400), (1024, 768)]     # more than 512 blocks: strips
 
 
 @pytest.mark.parametrize("lam", [0.2, 1.0])

@@ -19,7 +19,7 @@ def test_bad_pixels_stay_in_their_windows(bad, where):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     print(f"[gpu] photo pixels {bad} in {where}", flush=True)
-    W, H = 1100, 800          # 875 blocks: strips
+    W, H = 1500, 1000         # more than 512 blocks: strips
     sc = synth.random_scene(side=2, views=1, width=8, height=8, seed=1)
     cam = sc.cams[0]
     sc.cams = [synth.Camera(cam.R, cam.t, 100.0, 100.0, W / 2, H / 2, W, H)]
@@ -35,7 +35,7 @@ def test_bad_pixels_stay_in_their_windows(bad, where):
     r.loss_photo(target, 0.2)
     _, G = reference(image, target, [(W, H)], 0.2)
     got, ok = r.dL_dimage.double(), torch.isfinite(G)
-    assert 0.97 * G.numel() < int(ok.sum()) < G.numel()
+    assert 0.98 * G.numel() < int(ok.sum()) < G.numel()
     got, G = got[ok], G[ok]
     assert bool(torch.isfinite(got).all())
     assert float(((got - G).abs() / torch.clamp(G.abs(), min=float(0.01 * G.abs().max()))).max()) <= 1e-3

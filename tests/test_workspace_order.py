@@ -2,7 +2,8 @@
 largest call serves every smaller one: instance capacities and record counts around
 the limits of the sort's small radix work-groups (2^18 pairs) and of views sorted
 apart (2^17 and 2^18 records), Gaussians around 32 per pixel of the pruning's map.
-On the host, with the runtime's calls stood in for."""
+And the photometric loss's holds the sums of every strip its rule
+of view sizes takes.  On the host, with the runtime's calls stood in for."""
 from fake_hip import run
 
 SORT = """
@@ -43,3 +44,34 @@ def test_sort_workspace_grows_with_capacity_and_records(tmp_path):
 
 def test_prune_workspace_grows_with_the_gaussians(tmp_path):
     run(tmp_path, PRUNE)
+
+
+PHOTO = """
+import math, random
+import numpy as np, synth
+from test_gpu_photo_rule import rows_of
+rng = random.Random(1)
+tables = [[(32, 32)] * 600, [(64, 64)] * 200, [(54, 16)] * 600, [(1, 17)] * 600, [(640, 480)] * 3, [(33, 33)] * 130]
+for _ in range(300):
+    size = lambda: (int(math.exp(rng.uniform(0, 7))), int(math.exp(rng.uniform(0, 7))))
+    tables.append([size()] * rng.randint(1, 600) if rng.random() < 0.5 else [size() for _ in range(rng.randint(1, 200))])
+heights = set()
+for t in tables:
+    cams = []
+    for w, h in t:
+        c = synth.pinhole(np.eye(3), np.zeros(3), w, h)
+        cams.append(c)
+    v = abi.pg_views_create(cams, 1, 10, 0, abi.make_tiling())
+    b = C.c_size_t()
+    assert lib.pg_photo_workspace_size(v, C.byref(b)) == 0
+    rows = rows_of(t)
+    heights.add(rows)
+    sums = sum(-(-w // 54) * -(-h // rows) for w, h in t) if rows else sum(-(-w // 32) * -(-h // 32) for w, h in t)
+    assert b.value >= 16 * sums, (t[:3], len(t), rows)
+    abi.pg_views_destroy(v)
+assert heights == {0, 16, 32, 64, 192}, heights
+"""
+
+
+def test_photo_workspace_holds_every_strip(tmp_path):
+    run(tmp_path, PHOTO)
