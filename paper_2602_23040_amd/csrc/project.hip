@@ -500,9 +500,11 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 //     from the middle out, eight mask bytes per load, with q <= 9 in FP64 at
 //     the centres whose mask is set.  The label is exactly that of a scan of
 //     every pixel of the square.  (One lane per record waits for the largest
-//     box among 64: 730 us against 482.)  Squares past kFlowSide are scanned by
-//     the whole wave, 64 pixels per round, only in tiles that hold motion (and only
-//     if a cell under them does).
+//     box among 64: 730 us against 482.)  Squares past kFlowSide, if a
+//     cell under them holds motion, are scanned by a whole wave, 64 pixels per
+//     round, only in tiles that hold motion, which are found eight a load.  They are
+//     dealt to the four waves: the collected list's first wave would hold most of
+//     them, and the others wait.
 // A hit writes 1 to the Gaussian's zeroed label: every writer stores the same
 // value, so the OR over views needs no atomics.  A Gaussian's chunk runs on one
 // XCD for every view, so its parameters and labels stay in that L2.
@@ -510,10 +512,17 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 // with the FP64 projection of every record and a wave per flagged record; 575
 // with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles;
 // 339 with the unlabelled records collected and the next one's parameters read
-// ahead.
+// ahead.  Larger Gaussians, 2.4 M records of 10 views, 3 % of motion: 638 us by the
+// projection of every record, 1,098 with large squares walked by the wave that
+// collected them, 548.
 constexpr int kFlowThreads = 256;
 constexpr int kFlowRecs = 2048;        // Gaussians per work-group at most
 constexpr int64_t kFlowFill = 2048;    // work-groups that fill the chip
+// LDS left unused, so that five groups share a CU: with six (as the registers allow) so
+// many views run beside each other that each sees fewer labels of the others (50 views
+// of 276 k Gaussians, all motion, four / five / six groups: 423 / 440 / 525 us; 5 %: 322 / 302
+// / 291).
+constexpr int kFlowSpare = 6144;
 constexpr int kFlowSide = 64;          // largest side of a square that eight lanes scan
 
 // Eight mask bytes from p on (zero past the end of the masks).
@@ -581,13 +590,14 @@ __global__ __launch_bounds__(256) void k_tile_motion(const ViewDev* __restrict__
 // (the same Gaussians without motion: 352 us with an FP64 projection each and a load per
 // tile, 549 with the two phases and a load per tile, 169).
 constexpr int kMotionWide = 6;
+template <bool WIDE>
 __device__ __forceinline__ bool motion_under(const ViewDev& V, const uint8_t* __restrict__ tmot, int64_t n_tiles,
                                              int32_t x0, int32_t x1, int32_t y0, int32_t y1, int32_t tw, int32_t th) {
     const int32_t runs = tw / 8, sx = __builtin_ctz(tw), sy = __builtin_ctz(th);
     const uint32_t rep = runs == 1 ? 0xffu : (runs == 2 ? 0x55u : 0x11u);       // a row's columns in every row
     const int32_t tx0 = x0 >> sx, tx1 = x1 >> sx;
     uint32_t any = 0;
-    if (tx1 - tx0 >= kMotionWide) {
+    if (WIDE && tx1 - tx0 >= kMotionWide) {
         const uint64_t left = ((2u << (runs - 1)) - (1u << ((x0 - (tx0 << sx)) >> 3))) * rep;
         const uint64_t right = ((2u << ((x1 - (tx1 << sx)) >> 3)) - 1u) * rep;
         for (int32_t ty = y0 >> sy; ty <= y1 >> sy; ty++) {
@@ -665,14 +675,14 @@ __device__ __forceinline__ bool flow_may_hit(const ViewDev& V, float rn2, const 
     // half sides of up to 256 tested here 1,801, 128 1,702, 64 1,532)
     if (!(rx < 64.0f && ry < 64.0f && fabsf(px) < 1e8f && fabsf(py) < 1e8f)) return true;
     const int32_t x0 = (int32_t)fmaxf(fx0, 0.0f), y0 = (int32_t)fmaxf(fy0, 0.0f);
-    return motion_under(V, tmot, n_tiles, min(x0, V.W - 1), min((int32_t)fx1, V.W - 1), min(y0, V.H - 1), min((int32_t)fy1, V.H - 1),
+    return motion_under<true>(V, tmot, n_tiles, min(x0, V.W - 1), min((int32_t)fx1, V.W - 1), min(y0, V.H - 1), min((int32_t)fy1, V.H - 1),
                         tw, th);
 }
 
 // A record's clipped square and quadratic form (x1 < x0: nothing to scan).
 struct Square {
     double mx, my, A, B, C;
-    int32_t x0, y0, x1, y1;
+    int32_t x0, y0, x1, y1;     // y1 negative (of a square that is not empty): ~y1 of a large one
 };
 
 __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __restrict__ views, int32_t nv, int32_t C,
@@ -766,11 +776,9 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
         const int32_t at = base + (int32_t)threadIdx.x;
         bool large = false;
         int32_t ix0 = 0, ix1 = -1, iy0 = 0, iy1 = -1;
-        int64_t out = 0;
         double mx = 0.0, my = 0.0, A = 1.0, B = 0.0, Cq = 1.0;
         if (at < count) {
             const int64_t i = i0 + s_rec[at];
-            out = out0 + i;
             float rec[11];
 #pragma unroll
             for (int k = 0; k < 11; k++) rec[k] = P0[(int64_t)k * N + i];
@@ -803,7 +811,10 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
                         iy0 = max(iy0, (int32_t)ceilf((float)(my - 0.5 - (double)ey) - 0.01f));
                         iy1 = min(iy1, (int32_t)floorf((float)(my - 0.5 + (double)ey) + 0.01f));
                     }
-                    if (ix0 > ix1 || iy0 > iy1 || !motion_under(V, tmot, n_tiles, ix0, ix1, iy0, iy1, tw, th)) {
+                    const bool motion = large ? motion_under<true>(V, tmot, n_tiles, ix0, ix1, iy0, iy1, tw, th)
+                                              : ix0 <= ix1 && iy0 <= iy1 &&
+                                                    motion_under<false>(V, tmot, n_tiles, ix0, ix1, iy0, iy1, tw, th);
+                    if (!motion) {
                         large = false;
                         ix1 = ix0 - 1;
                     }
@@ -812,13 +823,13 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
         }
         // eight lanes per record: each takes every eighth row, from the middle out
         __syncthreads();        // the previous step's records are done with
-        s_sq[threadIdx.x] = {mx, my, A, B, Cq, ix0, iy0, large ? ix0 - 1 : ix1, iy1};
+        s_sq[threadIdx.x] = {mx, my, A, B, Cq, ix0, iy0, ix1, large ? ~iy1 : iy1};
         __syncthreads();
         const int32_t sub = lane % 8;
         for (int32_t r = threadIdx.x / 8; r < kFlowThreads && base + r < count; r += kFlowThreads / 8) {
             const Square q = s_sq[r];
             const int32_t n = q.x1 - q.x0 + 1;
-            if (n <= 0) continue;         // culled, no motion, or left to the whole wave
+            if (n <= 0 || q.y1 < 0) continue;         // culled, no motion, or left to the whole wave
             const int32_t mid = min(max((int32_t)q.my, q.y0), q.y1);      // |mean| is finite: the square is not empty
             const int32_t last = 2 * max(q.y1 - mid, mid - q.y0);         // rows mid, mid + 1, mid - 1, mid + 2, ...
             const int64_t p0 = V.pix_base + q.x0;
@@ -843,34 +854,41 @@ __global__ __launch_bounds__(kFlowThreads) void k_flow_mask(const ViewDev* __res
             }
             if (hit) dyn_gauss[out0 + i0 + s_rec[base + r]] = 1;      // every writer stores the same value
         }
-        // squares too large for that: all lanes on one record
-        uint64_t todo = __ballot(large);
+        // squares too large for that: all lanes on one record, the records dealt to the waves
+        // (the list's first wave alone would hold most of them)
+        const int wave = (int)threadIdx.x / 64, mine = 4 * lane + wave;
+        uint64_t todo = __ballot(base + mine < count && s_sq[mine].x1 >= s_sq[mine].x0 && s_sq[mine].y1 < 0);
         while (todo) {
-            const int src = __builtin_ctzll(todo);
+            const int32_t r = 4 * __builtin_ctzll(todo) + wave;
             todo &= todo - 1;
-            const int32_t sx0 = __shfl(ix0, src, 64), sx1 = __shfl(ix1, src, 64);
-            const int32_t sy0 = __shfl(iy0, src, 64), sy1 = __shfl(iy1, src, 64);
-            const double smx = __shfl(mx, src, 64), smy = __shfl(my, src, 64);
-            const double sA = __shfl(A, src, 64), sB = __shfl(B, src, 64), sC = __shfl(Cq, src, 64);
+            const Square q = s_sq[r];
+            const int32_t sx0 = __builtin_amdgcn_readfirstlane(q.x0), sx1 = __builtin_amdgcn_readfirstlane(q.x1);
+            const int32_t sy0 = __builtin_amdgcn_readfirstlane(q.y0), sy1 = ~__builtin_amdgcn_readfirstlane(q.y1);
             const uint8_t* M = masks + V.pix_base;
-            const int32_t per_tile = tw * th;
+            const int32_t kx = __builtin_ctz(tw), ky = __builtin_ctz(th);
             bool any = false;
-            for (int32_t ty = sy0 / th; ty <= sy1 / th && !any; ty++) {
-                for (int32_t tx = sx0 / tw; tx <= sx1 / tw && !any; tx++) {
-                    if (!tmot[V.tile_base + (int64_t)ty * V.TX + tx]) continue;
-                    for (int32_t b = 0; b < per_tile && !any; b += 64) {
-                        const int32_t p = b + lane;
-                        const int32_t x = tx * tw + p % tw, y = ty * th + p / tw;
-                        bool hit = false;
-                        if (p < per_tile && x >= sx0 && x <= sx1 && y >= sy0 && y <= sy1 && M[(int64_t)y * V.W + x]) {
-                            tests++;
-                            hit = q_at(sA, sB, sC, ((double)x + 0.5) - smx, ((double)y + 0.5) - smy) <= 9.0;
+            for (int32_t ty = sy0 >> ky; ty <= sy1 >> ky && !any; ty++) {
+                for (int32_t t8 = sx0 >> kx; t8 <= sx1 >> kx && !any; t8 += 8) {      // eight tiles a load
+                    const uint64_t w = first_bytes(mask8(tmot, V.tile_base + (int64_t)ty * V.TX + t8, n_tiles),
+                                                   (sx1 >> kx) - t8 + 1);
+                    uint64_t moving = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(w >> 32)) << 32 |
+                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+                    while (moving && !any) {
+                        const int32_t k = __builtin_ctzll(moving) >> 3, tx = t8 + k;
+                        moving &= ~(0xffull << (8 * k));
+                        for (int32_t p = lane; p < 256 && !any; p += 64) {       // a tile is 256 pixels
+                            const int32_t x = (tx << kx) + (p & (tw - 1)), y = (ty << ky) + (p >> kx);
+                            bool hit = false;
+                            if (x >= sx0 && x <= sx1 && y >= sy0 && y <= sy1 && M[(int64_t)y * V.W + x]) {
+                                tests++;
+                                hit = q_at(q.A, q.B, q.C, ((double)x + 0.5) - q.mx, ((double)y + 0.5) - q.my) <= 9.0;
+                            }
+                            any = __ballot(hit) != 0;
                         }
-                        any = __ballot(hit) != 0;
                     }
                 }
             }
-            if (any && lane == src) dyn_gauss[out] = 1;
+            if (any && lane == 0) dyn_gauss[out0 + i0 + s_rec[base + r]] = 1;
         }
     }
     if (counters) {
@@ -1376,7 +1394,7 @@ hipError_t launch_flow_mask(const pg_views* v, const float* params, const uint8_
         // Groups of one or two rounds run beside each other and see no labels yet (collecting
         // there: 30 views of 72 k Gaussians 139 / 142 us, 2 of 432 k 107 / 110).
         const int32_t open = 8 * per * v->n_views > 2 * kFlowFill;
-        k_flow_mask<<<(unsigned)(8 * per * v->n_views), kFlowThreads, 0, s>>>(
+        k_flow_mask<<<(unsigned)(8 * per * v->n_views), kFlowThreads, kFlowSpare, s>>>(
             v->d_views, v->n_views, v->channels, v->n_gauss, recs, open, v->n_tiles, v->n_pixels, v->tiling.tile_w, v->tiling.tile_h,
             params, masks, tile_motion, dyn_gauss, reinterpret_cast<unsigned long long*>(counters));
     }
