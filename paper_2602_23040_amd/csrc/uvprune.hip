@@ -19,7 +19,7 @@
 // comes out ordered by opacity and then id; a Gaussian's rank is its distance
 // from the start of its run.  Without the flag they find no pairs and each of
 // their launches ends at once (about 2 us).  1.26 M Gaussians of two frames, 5 a
-// pixel: 161 us against 234 by the sorts, 4 k to 90 k Gaussians 48 to 52 against 60
+// pixel: 160 us against 234 by the sorts, 4 k to 90 k Gaussians 48 to 52 against 60
 // to 101 (the sorts with their words cleared by the kernels before them; 240, and 87
 // to 121 without).
 #include "pg_internal.h"
@@ -78,27 +78,26 @@ __global__ __launch_bounds__(kT) void k_uv_init(const int64_t* __restrict__ n_de
 // A work-group counts its Gaussians in an LDS table of pixels first and adds each pixel's
 // number to the pixel's count once: additions to one address take 11 ns each, and a map
 // may have most of its Gaussians in a few pixels (1.26 M Gaussians, all in one pixel:
-// 13,960 -> 234 us for the call, half of them in 200: 620 -> 390; the sorts alone 209 and
-// 236).  Once a list is known to be too long the counts are of no use and are left
-// alone.  Few Gaussians take small work-groups, which spread over the chip.
-constexpr int64_t kKeyFew = 1 << 18;
-template <int KEY>
-__global__ __launch_bounds__(KEY) void k_uv_key(const float* __restrict__ params, const int64_t* __restrict__ n_dev,
+// 13,960 -> 260 us for the call, half of them in 200: 620 -> 398; the sorts alone 209 and
+// 236; with 1,024 Gaussians a group 235 and 390, but 164 against 160 on an even map).  Once a
+// list is known to be too long the counts are of no use and are left alone.
+constexpr int kKey = 256;
+__global__ __launch_bounds__(kKey) void k_uv_key(const float* __restrict__ params, const int64_t* __restrict__ n_dev,
                                                int64_t n_cap, int32_t F, int32_t C, int32_t M, int32_t Nv,
                                                const int32_t* __restrict__ expected, int32_t* __restrict__ uv,
                                                uint32_t* __restrict__ okey, int32_t* __restrict__ oval,
                                                int32_t* __restrict__ count, int32_t* __restrict__ slot,
                                                int64_t* __restrict__ cnt) {
-    constexpr int kTable = 2 * KEY;
+    constexpr int kTable = 2 * kKey;
     __shared__ int32_t s_pixel[kTable], s_count[kTable];
     __shared__ int32_t s_listed, s_long;
     const int64_t n = imin(*n_dev, n_cap);
-    const int64_t j = (int64_t)blockIdx.x * KEY + threadIdx.x;
-    if ((int64_t)blockIdx.x * KEY >= (int64_t)F * n) return;
+    const int64_t j = (int64_t)blockIdx.x * kKey + threadIdx.x;
+    if ((int64_t)blockIdx.x * kKey >= (int64_t)F * n) return;
     const bool has = j < (int64_t)F * n;
     if (count) {
         if (threadIdx.x == 0) s_long = 0;
-        for (int k = threadIdx.x; k < kTable; k += KEY) {
+        for (int k = threadIdx.x; k < kTable; k += kKey) {
             s_pixel[k] = -1;
             s_count[k] = 0;
         }
@@ -137,7 +136,7 @@ __global__ __launch_bounds__(KEY) void k_uv_key(const float* __restrict__ params
     uint32_t h = 0;
     int32_t at = 0;
     if (key >= 0) {
-        // at most KEY of the table's entries are ever taken, so the walk ends
+        // at most kKey of the table's entries are ever taken, so the walk ends
         h = ((uint32_t)pixel * 2654435761u) % kTable;
         for (;; h = (h + 1) % kTable) {
             const int32_t was = atomicCAS(&s_pixel[h], -1, pixel);
@@ -146,7 +145,7 @@ __global__ __launch_bounds__(KEY) void k_uv_key(const float* __restrict__ params
         at = atomicAdd(&s_count[h], 1);
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kTable; k += KEY) {
+    for (int k = threadIdx.x; k < kTable; k += kKey) {
         const int32_t mine = s_count[k];
         if (mine == 0) continue;
         const int32_t before = atomicAdd(&count[s_pixel[k]], mine);
@@ -348,10 +347,8 @@ hipError_t launch_uv_prune(const float* params, const int64_t* n_dev, int64_t n_
     const unsigned grid = (unsigned)ceil_div(n, kT);
     const int pixel_bits = key_bits_for(pixels + 1);
     hipError_t e = hipSuccess;
-    const int key_threads = n <= kKeyFew ? 256 : 1024;
-    auto* key = n <= kKeyFew ? k_uv_key<256> : k_uv_key<1024>;
-    key<<<(unsigned)ceil_div(n, key_threads), key_threads, 0, s>>>(params, n_dev, n_cap, F, C, M, Nv, expected, uv,
-                                                                   w.ka, w.va, lists ? w.start : nullptr, rank, w.cnt);
+    k_uv_key<<<(unsigned)ceil_div(n, kKey), kKey, 0, s>>>(params, n_dev, n_cap, F, C, M, Nv, expected, uv, w.ka, w.va,
+                                                          lists ? w.start : nullptr, rank, w.cnt);
     if (lists) {
         k_uv_place<<<(unsigned)ceil_div(pixels, kPlace), kPlace, 0, s>>>(w.cnt, w.start, pixels, w.place);
         k_uv_scatter<<<grid, kT, 0, s>>>(w.cnt, n_cap, M, Nv, w.ka, w.va, uv, rank, w.place, (uint64_t*)w.kb);

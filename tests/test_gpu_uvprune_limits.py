@@ -1,7 +1,7 @@
 """UV pruning on both sides of the limits between pixel lists and sorts: one long list
 (256 entries), the comparisons of many lists (128 a Gaussian as counted, 64 as
-expected of an even map), the pixels of the map (2^22), and the Gaussians of the
-key kernel's two work-groups (2^18), each with crowded pixels.  Pixels, ranks and
+expected of an even map), the pixels of the map (2^22), and 2^18 Gaussians, each
+with crowded pixels.  Pixels, ranks and
 flags are integers and must equal the oracle's."""
 import numpy as np
 import pytest
