@@ -19,7 +19,7 @@
 //  - the row's (x, y) goes to LDS, and each lane adds its 11 horizontal taps of x,
 //    d = x - y, d^2 and x y (four window sums instead of five: s_x + s_y - 2 s_xy
 //    is the variance of d; the products are formed per tap, since 16-byte rows
-//    of them made LDS reads the limit: 596 us against 494);
+//    of them made LDS reads the limit, a fifth slower);
 //  - vertical windows are running sums: a new row adds its term to the ten
 //    windows under way and completes the oldest (acc[k] = acc[k + 1] + w h, one
 //    multiply-add and no shift);
@@ -44,7 +44,7 @@
 // instructions a row and loses a digit in flat areas beside texture.)  Three waves, one per channel, share a work-group; per-strip sums
 // of S and |I - T| (FP64) go to a small partial array that k_photo_final reduces.
 //
-// Bound by FP32 VALU issue, about 300 instructions per lane and row: the strip's
+// Bound by FP32 VALU issue, about 310 instructions per lane and row: the strip's
 // 64 lanes give 54 columns and its rows run 20 ahead of the first output, 1.3
 // times the work without halos.  16 views of 1024x768: 754 us by 32 x 32 blocks in
 // LDS (every tap of both passes read from there), 433 by strips (414 before d was

@@ -512,7 +512,7 @@ void k_project(const ViewDev* __restrict__ views, const int32_t* __restrict__ fr
 // with the FP64 projection of every record and a wave per flagged record; 575
 // with the two phases; 430 with cells of 8 x 4 pixels instead of whole tiles;
 // 339 with the unlabelled records collected and the next one's parameters read
-// ahead.  Larger Gaussians, 2.4 M records of 10 views, 3 % of motion: 638 us by the
+// ahead; 329 now, of which the motion cells 25 and the fetch 42.  Larger Gaussians, 2.4 M records of 10 views, 3 % of motion: 638 us by the
 // projection of every record, 1,098 with large squares walked by the wave that
 // collected them, 548.
 constexpr int kFlowThreads = 256;
